@@ -29,7 +29,7 @@
 // block.  Accumulator element r of lane l is output row
 // 8 (r / 4) + 4 (l / 32) + (r % 4), column l % 32.
 
-#include "sharq_device.hpp"
+#include "sharq_dequant16.hpp"
 #include <type_traits>
 
 namespace sharq {
@@ -1701,8 +1701,6 @@ static hipError_t go_skinny_dt(int ydt, const uint8_t* spc, const uint8_t* spm, 
 // bf16 32x32x16 operand layout: lane l holds row l % 32 and K values
 // 8 (l / 32) + 0..7; the accumulator layout is that of the FP4 MFMA.
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
 __device__ __forceinline__ int swz_nv(int row) { return ((row >> 1) ^ (row >> 3)) & 3; }
 
 // Eight E2M1 codes (one dword, lower K in the lower nibble) times scale d ->
@@ -1723,12 +1721,6 @@ __device__ __forceinline__ uint4 dequant8_bf16(uint32_t codes, float d) {
     o[i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
   }
   return make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 q) {
-  bf16x8 v;
-  __builtin_memcpy(&v, &q, 16);
-  return v;
 }
 
 struct NvA {         // one lane's activation data for one 32-position block
@@ -1906,35 +1898,6 @@ struct NvWRaw {         // one weight row of one step
 };
 
 constexpr int kNvStage = 256 * 64;   // fp16 weight tile of one step: 256 rows x 32 positions
-
-// Pieces of the exact dequantization q * d in fp16: codes byte SEL (two
-// E2M1 values, lower position in the low nibble) -> one packed fp16 pair.
-// Every such product is exact in fp16: q has at most 2 significant bits and
-// |q| <= 6, an E4M3 scale d has at most 4 and lies in [2^-9, 448], so q d has
-// at most 6 significant bits and lies in [2^-10, 2688], inside fp16's normal
-// range.  The FP4 pair is decoded to fp16 and scaled by one packed fp16
-// multiply (two values per instruction), half the work of decoding to fp32,
-// scaling and packing to bf16.
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ f16x8 as_f16x8(uint4 q) {
-  f16x8 v;
-  __builtin_memcpy(&v, &q, 16);
-  return v;
-}
-
-// an E4M3 scale as an fp16 pair (exact)
-__device__ __forceinline__ f16x2 nv_scale2(uint32_t code) {
-  const _Float16 h = (_Float16)e4m3_value(code);
-  return f16x2{h, h};
-}
-
-template <int SEL>
-__device__ __forceinline__ uint32_t f16_pair(uint32_t codes, f16x2 d) {
-  const f16x2 v = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, SEL);
-  return __builtin_bit_cast(uint32_t, v * d);
-}
 
 // PAT 0: a.spc is the dense backbone copy (16 bytes per block, block-major).
 template <int PAT>
@@ -2184,6 +2147,13 @@ __device__ __forceinline__ void tile_nv_il(const uint8_t* sp_codes, const uint8_
 
 static int device_cus();   // compute units of the current device (host launchers below)
 
+// The small-M kernel of the formats on 16-bit MFMA (sharq_skinny16.hip).
+bool use_skinny16(bool nv, int64_t M, int N, int K);
+hipError_t launch_linear_skinny16(bool nv, int pat, int ydt, const uint8_t* spc, const uint8_t* spm,
+                                  const uint8_t* sps, const uint8_t* dnc, const uint8_t* dns, const float* tsx,
+                                  int64_t M, const uint8_t* wc, const uint8_t* ws, const float* tsw, int N, int K,
+                                  void* Y, int64_t ldy, hipStream_t st);
+
 // Persistent: at most one workgroup per CU walks the tiles b, b + G, ... in
 // the XCD-aware order of tile_at (any grid: the Qwen2.5-7B shapes have 148
 // and 14 column tiles; measured neutral there, where the dequantization and
@@ -2239,7 +2209,11 @@ hipError_t launch_linear_nv(int pat, int ydt, const uint8_t* spc, const uint8_t*
                             const uint8_t* dnc, const uint8_t* dns, const float* tsx, int64_t M, const uint8_t* wc,
                             const uint8_t* ws, const float* tsw, int N, int K, void* Y, int64_t ldy,
                             const uint8_t* spd, hipStream_t st) {
-  if (spd && K % kBK == 0) return go_nv_dt<0>(ydt, spd, nullptr, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);
+  const bool dense = spd && K % kBK == 0;
+  if ((dense || spc != nullptr) && use_skinny16(true, M, N, K))
+    return launch_linear_skinny16(true, dense ? 0 : pat, ydt, dense ? spd : spc, spm, sps, dnc, dns, tsx, M, wc, ws,
+                                  tsw, N, K, Y, ldy, st);
+  if (dense) return go_nv_dt<0>(ydt, spd, nullptr, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);
   if (spc == nullptr) return hipErrorInvalidValue;   // rejected by the C ABI (K not a multiple of 128)
   return pat == 24 ? go_nv_dt<24>(ydt, spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st)
                    : go_nv_dt<48>(ydt, spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);
@@ -2902,6 +2876,9 @@ hipError_t launch_linear_slots(int mode, int pat, int ydt, bool nv, const uint8_
 hipError_t launch_linear_hif4(int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
                               const uint8_t* dns, int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K,
                               void* Y, int64_t ldy, hipStream_t st) {
+  if (use_skinny16(false, M, N, K))
+    return launch_linear_skinny16(false, 24, ydt, spc, spm, sps, dnc, dns, nullptr, M, wc, ws, nullptr, N, K, Y, ldy,
+                                  st);
   const int gx = (N + 255) / 256, gy = (int)((M + kBM - 1) / kBM);
   const dim3 grid((unsigned)(gx * gy)), block(256);
   if (ydt == 2)
