@@ -23,6 +23,9 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 q) { return __builtin_bit_cast(bf16x8, q); }
 __device__ __forceinline__ f16x8 as_f16x8(uint4 q) { return __builtin_bit_cast(f16x8, q); }
 
+// Place of the 16-byte parts of a row of 32 staged 16-bit values (64 bytes)
+__device__ __forceinline__ int swz_nv(int row) { return ((row >> 1) ^ (row >> 3)) & 3; }
+
 // an E4M3 scale as an fp16 pair (exact)
 __device__ __forceinline__ f16x2 nv_scale2(uint32_t code) {
   const _Float16 h = (_Float16)e4m3_value(code);
@@ -40,6 +43,25 @@ __device__ __forceinline__ uint32_t f16_pair(uint32_t codes, f16x2 d) {
 // eight codes -> eight fp16 values
 __device__ __forceinline__ uint4 nv_dequant8(uint32_t codes, f16x2 d) {
   return make_uint4(f16_pair<0>(codes, d), f16_pair<1>(codes, d), f16_pair<2>(codes, d), f16_pair<3>(codes, d));
+}
+
+// Eight codes times scale d -> eight bf16 values.  The fp32 products have at
+// most 6 significant bits, so dropping the low 16 bits is exact.
+__device__ __forceinline__ uint4 dequant8_bf16(uint32_t codes, float d) {
+  uint32_t o[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v2f v;
+    switch (i) {
+      case 0: v = fp4x2_decode<0>(codes); break;
+      case 1: v = fp4x2_decode<1>(codes); break;
+      case 2: v = fp4x2_decode<2>(codes); break;
+      default: v = fp4x2_decode<3>(codes); break;
+    }
+    const float a = v.x * d, b = v.y * d;
+    o[i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+  }
+  return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
 // The two scales E6M2 * 2^(E1_8 + E1_16) of dword t (positions 8 t .. 8 t + 7,

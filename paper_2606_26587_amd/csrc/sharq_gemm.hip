@@ -29,13 +29,11 @@
 // block.  Accumulator element r of lane l is output row
 // 8 (r / 4) + 4 (l / 32) + (r % 4), column l % 32.
 
-#include "sharq_dequant16.hpp"
+#include "sharq_tile.hpp"
 #include <type_traits>
 
 namespace sharq {
 
-constexpr int kBM = 128;          // tile rows: 4 wavefronts x 32
-constexpr int kBK = 128;          // K per step: 4 scale blocks, 64 bytes of codes per row
 constexpr int kLdsStride = 80;    // bytes per staged weight row (64 + 16 to spread LDS banks)
 constexpr int kSkinnyMaxM = 32;   // activation rows up to which the small-M kernel runs
 constexpr int kSkinnyMaxRowTiled = 256;   // ... and, when the main kernel has few tiles, up to this many
@@ -57,16 +55,6 @@ struct AStep {
   uint32_t spm[2];   // backbone metadata
   uint32_t sdn, ssp; // E8M0 scales of the step's 4 blocks (byte j = block 4 ks + j)
   uint4 spd[2];      // the dense backbone codes instead (pattern 0: a dense copy was prepared)
-};
-
-// Activation rows live in panel-major buffers: K is cut into panels of 128
-// positions (one K step; the last panel may be narrower) and panel p stores
-// all R rows' bytes for its K range back to back, so the 32 rows of a
-// wavefront are 2 KB (codes), 1 KB (backbone), 512 B (metadata) and 128 B
-// (scales) of contiguous memory per step.
-struct ARow {
-  const uint8_t *dn, *spc, *spm, *dns, *sps;   // buffer bases
-  int64_t r, R;                                // this lane's activation row, rows in the buffers
 };
 
 template <bool SCALE_DW>
@@ -234,15 +222,6 @@ __device__ __forceinline__ void step_mx(v16f (&acc)[NF], const AStep& cur, const
   }
 }
 
-template <typename OutT>
-__device__ __forceinline__ void store_out(OutT* p, float v);
-template <>
-__device__ __forceinline__ void store_out<float>(float* p, float v) { *p = v; }
-template <>
-__device__ __forceinline__ void store_out<uint16_t>(uint16_t* p, float v) { *p = f32_to_bf16_rne(v); }
-template <>
-__device__ __forceinline__ void store_out<_Float16>(_Float16* p, float v) { *p = (_Float16)v; }
-
 // One 128 x (32 NF) output tile.  Rows of the tile are output rows
 // [row_lo, row_lo + 128) clipped at row_hi; the activation row of output row
 // i is row_index[i] when row_index is given, else i - out_base + act_base.
@@ -356,8 +335,6 @@ struct AOps {        // MFMA-ready activation operands of one K step
   uint32_t ssp, sdn; // E8M0 scale dwords shifted to this lane's half
 };
 
-#define SHARQ_FENCE() __builtin_amdgcn_sched_barrier(0)
-
 constexpr int kStageW = 256 * kLdsStride;        // weight codes of one stage
 constexpr int kStageBytes = kStageW + 64 * 16;   // + the 64 scale records
 
@@ -389,7 +366,6 @@ __device__ __forceinline__ uint32_t expand48_lut(uint32_t c16, uint2 sel) {
 __device__ __forceinline__ void lut48_fill(uint2* lut) {
   if (threadIdx.x < 256) lut[threadIdx.x] = lut48_entry(threadIdx.x);
 }
-
 
 // Piece Q (0..15) of the next step's expanded backbone: block Q / 8, output
 // dword (Q % 8) / 2, 16-bit half Q % 2 (returned in place within the dword).
@@ -456,37 +432,6 @@ __device__ __forceinline__ void mma_dn(v16f (&acc)[NF], const AOps& a, const uin
   acc[F] = mfma_fp4<(F & 1) ? 2 + SUB : SUB, SUB>(as_operand(b[F]), as_operand(a.dn[SUB]), acc[F], bw[F >> 1],
                                                  a.sdn);
 }
-
-template <typename OutT>
-struct Vec4Out;
-template <>
-struct Vec4Out<float> {
-  static __device__ __forceinline__ void put(float* p, float a, float b, float c, float d) {
-    *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
-  }
-  static constexpr int kAlign = 16;
-};
-template <>
-struct Vec4Out<uint16_t> {
-  static __device__ __forceinline__ void put(uint16_t* p, float a, float b, float c, float d) {
-    // v_cvt_pk_bf16_f32: two round-to-nearest-even conversions per instruction
-    typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
-    bf4 v;
-    v[0] = (__bf16)a; v[1] = (__bf16)b; v[2] = (__bf16)c; v[3] = (__bf16)d;
-    *reinterpret_cast<bf4*>(p) = v;
-  }
-  static constexpr int kAlign = 8;
-};
-template <>
-struct Vec4Out<_Float16> {
-  static __device__ __forceinline__ void put(_Float16* p, float a, float b, float c, float d) {
-    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-    h4 v;
-    v[0] = (_Float16)a; v[1] = (_Float16)b; v[2] = (_Float16)c; v[3] = (_Float16)d;
-    *reinterpret_cast<h4*>(p) = v;
-  }
-  static constexpr int kAlign = 8;
-};
 
 template <int SUB, int F0, int F1, int NB>
 __device__ __forceinline__ void read_b(uint4 (&b)[NB], const uint8_t* lw, int lane) {
@@ -713,7 +658,6 @@ __device__ __forceinline__ void load_a_meta(AStep& s, const ARow& a, int ks, int
   s.ssp = *reinterpret_cast<const uint32_t*>(a.sps + pr * 4 + a.r * 4);
 }
 
-
 // Parts of one K step's global loads (K a multiple of 128), so that the
 // interleaved loop can spread them over its MFMA slots: the backbone codes
 // (or the dense copy) and the two scale dwords of the activations; two halves
@@ -781,84 +725,8 @@ __device__ __forceinline__ void store_w_stage(const WStep<NF>& w, uint8_t* stage
   }
 }
 
-// Epilogue of a wavefront's 32 x 256 block of 2-byte outputs through LDS.
-// In the accumulator layout a lane holds 8-byte pieces of one output row, so
-// direct stores put 32 scattered 16-byte pieces in every instruction (rows
-// are N outputs apart); measured on the Llama prefill shapes this cost about
-// 5 us per round of tiles.  Here the block is staged in LDS and read back
-// along rows: each store instruction then writes two whole 512-byte row
-// segments.  The wavefront owns its LDS region, and its LDS accesses execute
-// in order, so no barrier is needed inside.
-// A value that is the same in every lane, read from the first active one.
-__device__ __forceinline__ int64_t uniform64(int64_t x) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Fourth dword of a raw buffer resource (no stride, no swizzle, 32-bit
-// data format: the range check is on the byte offset).
-constexpr int kBufferWord3 = 0x00020000;
-typedef uint32_t v4u32_t __attribute__((ext_vector_type(4)));
-
-constexpr int kEpiStride = 528;            // bytes per staged row: 512 + 16 (spreads rows over banks)
-constexpr int kEpiWave = 32 * kEpiStride;  // one wavefront's region
 constexpr int kTileLds = 4 * kEpiWave > 3 * kStageBytes ? 4 * kEpiWave : 3 * kStageBytes;
 constexpr int kPersistLds = 3 * kStageBytes + 4 * kEpiWave;   // stages and epilogue apart: 129 KB
-
-template <typename OutT, int NF>
-__device__ __forceinline__ void store_tile_lds(const v16f (&acc)[NF], OutT* Y, int64_t ldy, int64_t row0,
-                                               int64_t row_hi, int n0, int N, uint8_t* buf, int lane) {
-  // a staged row is 64 NF bytes (+16); 4 NF lanes read it back, 16 / NF rows per instruction
-  constexpr int stride = 64 * NF + 16, lpr = 4 * NF, rpi = 64 / lpr;
-  const int r = lane & 31, half = lane >> 5;
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      Vec4Out<OutT>::put(reinterpret_cast<OutT*>(buf + r * stride + (32 * f + 8 * g + 4 * half) * 2),
-                         acc[f][4 * g], acc[f][4 * g + 1], acc[f][4 * g + 2], acc[f][4 * g + 3]);
-    }
-  }
-  // every read back first: a store under a per-row condition would take its
-  // read into its own branch and wait for it there, one LDS round trip per
-  // store
-  constexpr int kReads = 32 / rpi;
-  uint4 v[kReads];
-#pragma unroll
-  for (int i = 0; i < kReads; ++i)
-    v[i] = *reinterpret_cast<const uint4*>(buf + (rpi * i + lane / lpr) * stride + (lane % lpr) * 16);
-  // row0 and row_hi are the same in every lane; the compiler cannot see it,
-  // and a buffer resource held in vector registers would cost a loop over
-  // lanes around every store
-  row0 = uniform64(row0);
-  row_hi = uniform64(row_hi);
-  const int64_t rows = row_hi - row0 < 32 ? row_hi - row0 : 32;   // the wavefront's rows in the tile
-  if (rows <= 0) return;
-  const int64_t span = rows * ldy * (int64_t)sizeof(OutT);
-  const int ch = lane % lpr, col = n0 + 8 * ch;
-  if (span <= (int64_t)1 << 30) {
-    // Unconditional buffer stores over a range of exactly the wavefront's
-    // rows: the range check drops a store to a row past the tile, and a
-    // column past N gets an offset (2^31 - 16) past any such range.
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(Y + row0 * ldy, (short)0, (int)span,
-                                                                        kBufferWord3);
-#pragma unroll
-    for (int i = 0; i < kReads; ++i) {
-      const int rr = rpi * i + lane / lpr;
-      const int off = col < N ? (int)(((int64_t)rr * ldy + col) * (int64_t)sizeof(OutT)) : 0x7FFFFFF0;
-      v4u32_t q;
-      q[0] = v[i].x; q[1] = v[i].y; q[2] = v[i].z; q[3] = v[i].w;
-      __builtin_amdgcn_raw_buffer_store_b128(q, rs, off, 0, 0);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < kReads; ++i) {
-      const int rr = rpi * i + lane / lpr;
-      if (rr < rows && col < N) *reinterpret_cast<uint4*>(Y + (row0 + rr) * ldy + col) = v[i];
-    }
-  }
-}
 
 // One K step of a full (NF = 8) or half (NF = 4) tile; SPR: the load
 // schedule of step5.
@@ -987,41 +855,6 @@ __device__ __forceinline__ void il_main(v16f (&acc)[NF], IlSets<NF>& p, uint4 (&
   }
 }
 
-// Epilogue.  2-byte outputs go through the wavefront's LDS region `epi` as
-// whole row segments when the output allows 16-byte stores (every
-// workgroup-uniform condition); otherwise each lane stores its own row, four
-// consecutive columns per store.  The caller makes `epi` free.
-template <typename OutT, int NF>
-__device__ __forceinline__ void il_epilogue(const v16f (&acc)[NF], OutT* Y, int64_t ldy, int64_t row_lo,
-                                            int64_t row_hi, int n0, int N, uint8_t* epi, int wave, int lane) {
-  const int half = lane >> 5;
-  if constexpr (sizeof(OutT) == 2) {
-    if (((reinterpret_cast<uintptr_t>(Y) | (uintptr_t)(ldy * 2)) & 15u) == 0 && N % 8 == 0) {
-      store_tile_lds<OutT, NF>(acc, Y, ldy, row_lo + wave * 32, row_hi, n0, N, epi, lane);
-      return;
-    }
-  }
-  const int64_t row = row_lo + wave * 32 + (lane & 31);
-  if (row >= row_hi) return;
-  OutT* yr = Y + row * ldy;
-  const bool vec = ((reinterpret_cast<uintptr_t>(Y) | (uintptr_t)(ldy * (int64_t)sizeof(OutT))) &
-                    (uintptr_t)(Vec4Out<OutT>::kAlign - 1)) == 0;
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col = n0 + f * 32 + 8 * g + 4 * half;
-      if (vec && col + 3 < N) {
-        Vec4Out<OutT>::put(yr + col, acc[f][4 * g], acc[f][4 * g + 1], acc[f][4 * g + 2], acc[f][4 * g + 3]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (col + e < N) store_out<OutT>(yr + col + e, acc[f][4 * g + e]);
-      }
-    }
-  }
-}
-
 // This lane's activation row in a tile of rows [row_lo, row_hi): rows past
 // the end are clamped (loads stay in bounds, stores are masked).
 __device__ __forceinline__ int64_t il_row(const int32_t* row_index, int64_t row_lo, int64_t row_hi) {
@@ -1118,43 +951,6 @@ __device__ __forceinline__ void tiles_mx_il(const uint8_t* sp_codes, const uint8
   }
 }
 
-// Tile order.  Workgroups are dispatched round-robin over the 8 XCDs
-// (workgroup id mod 8), each with its own L2.  The ids are renumbered so that
-// each XCD walks a contiguous range of tiles, ordered in blocks of 4 M-tiles
-// x 8 N-tiles: the 32 workgroups an XCD runs at once then share 4 activation
-// tiles and 8 weight tiles in its L2.  Other grid shapes keep row-major order.
-__device__ __forceinline__ void tile_of(int id, int gx, int gy, int& mt, int& nt) {
-  const int total = gx * gy;
-  if ((gx & 7) == 0 && (gy & 3) == 0) {
-    const int per = total >> 3;
-    const int idp = (id & 7) * per + (id >> 3);
-    const int blk = idp >> 5, in = idp & 31;
-    const int bx = gx >> 3;
-    mt = (blk / bx) * 4 + (in & 3);
-    nt = (blk % bx) * 8 + (in >> 2);
-  } else {
-    mt = id / gx;
-    nt = id - mt * gx;
-  }
-}
-
-// The same order for any grid, for persistent loops: ids [0, 8 ceil(gx gy /
-// 8)) map one to one onto tile numbers, XCD x (id mod 8) taking a contiguous
-// range, walked in groups of 4 M-tiles, column by column (32 consecutive
-// numbers are 4 M-tiles x 8 N-tiles, as in tile_of, which this equals when
-// gx is a multiple of 8 and gy of 4).  False for the ids past the last tile.
-__device__ __forceinline__ bool tile_at(int id, int gx, int gy, int& mt, int& nt) {
-  const int total = gx * gy, per = (total + 7) >> 3;
-  const int u = (id & 7) * per + (id >> 3);
-  if (u >= total) return false;
-  const int g = u / (4 * gx), first = 4 * g;
-  const int gs = gy - first < 4 ? gy - first : 4;
-  const int in = u - g * 4 * gx;
-  mt = first + in % gs;
-  nt = in / gs;
-  return true;
-}
-
 // One tile per workgroup, for K not a multiple of 128 (the simpler pipeline
 // of tile_mx, which handles a narrow last panel).
 template <int NF, int PAT, bool SCALE_DW, typename OutT>
@@ -1189,15 +985,6 @@ __global__ __launch_bounds__(256) void k_linear_mx(const uint8_t* sp_codes, cons
 // runs a half tile instead of half of the CUs running a whole one (the
 // Llama qkv shape: 384 tiles on 256 CUs).  Half tile u covers tile t(u),
 // columns 128 h(u) on; with r a multiple of 8, t(u) keeps the XCD of u.
-__device__ __forceinline__ void half_unit(int u, int full, int halves, int& t, int& h) {
-  if ((halves & 15) == 0 && (full & 7) == 0) {
-    t = full + ((u >> 4) << 3) + (u & 7);
-    h = (u >> 3) & 1;
-  } else {
-    t = full + (u >> 1);
-    h = u & 1;
-  }
-}
 
 template <int PAT, typename OutT>
 __global__ __launch_bounds__(256) void k_linear_mx_persist(const uint8_t* sp_codes, const uint8_t* sp_meta,
@@ -1685,541 +1472,6 @@ static hipError_t go_skinny_dt(int ydt, const uint8_t* spc, const uint8_t* spm, 
 }
 
 // ---------------------------------------------------------------------------
-// NVFP4 two-path GEMM
-// ---------------------------------------------------------------------------
-//
-// NVFP4 block scales are E4M3 (not powers of two), which the block-scaled FP4
-// MFMA cannot apply, and the products q * d of an E2M1 code and an E4M3 scale
-// carry up to 6 significant bits -- exact in bf16 but not in FP8.  So both
-// operands are dequantized to bf16 (q * d, exact) and multiplied on
-// v_mfma_f32_32x32x16_bf16; the per-tensor scales S_x * S_w are applied once
-// in the epilogue.  One K step is one 32-position block.  Activation
-// fragments are dequantized in the registers of the wavefront that owns the
-// rows; the weight tile is dequantized once per workgroup into LDS (bf16,
-// 64 bytes per row, parts XOR-swizzled like the MXFP4 path).
-//
-// bf16 32x32x16 operand layout: lane l holds row l % 32 and K values
-// 8 (l / 32) + 0..7; the accumulator layout is that of the FP4 MFMA.
-
-__device__ __forceinline__ int swz_nv(int row) { return ((row >> 1) ^ (row >> 3)) & 3; }
-
-// Eight E2M1 codes (one dword, lower K in the lower nibble) times scale d ->
-// eight exact bf16 values (4 dwords).  The fp32 products have at most 6
-// significant bits, so dropping the low 16 bits is exact.
-__device__ __forceinline__ uint4 dequant8_bf16(uint32_t codes, float d) {
-  uint32_t o[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v2f v;
-    switch (i) {
-      case 0: v = fp4x2_decode<0>(codes); break;
-      case 1: v = fp4x2_decode<1>(codes); break;
-      case 2: v = fp4x2_decode<2>(codes); break;
-      default: v = fp4x2_decode<3>(codes); break;
-    }
-    const float a = v.x * d, b = v.y * d;
-    o[i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
-  }
-  return make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-struct NvA {         // one lane's activation data for one 32-position block
-  uint4 dn;          // residual codes
-  uint2 spc;         // compressed backbone codes
-  uint32_t spm;      // backbone metadata
-  uint32_t ssc;      // backbone E4M3 scale (byte 0)
-  uint32_t dsc;      // residual E4M3 scales of the two 16-halves (bytes 0, 1)
-};
-
-struct NvW {         // one thread's weight row for one block
-  uint4 codes;
-  uint32_t sc;
-};
-
-__device__ __forceinline__ void load_nv_a(NvA& s, const ARow& a, int ks, int K) {
-  const int p = ks >> 2, j = ks & 3, wp = min(128, K - 128 * p);
-  const int64_t pr = (int64_t)p * a.R;
-  s.dn = *reinterpret_cast<const uint4*>(a.dn + pr * 64 + a.r * (wp / 2) + 16 * j);
-  s.spc = *reinterpret_cast<const uint2*>(a.spc + pr * 32 + a.r * (wp / 4) + 8 * j);
-  s.spm = *reinterpret_cast<const uint32_t*>(a.spm + pr * 16 + a.r * (wp / 8) + 4 * j);
-  s.ssc = a.sps[pr * 4 + a.r * (wp / 32) + j];
-  s.dsc = *reinterpret_cast<const uint16_t*>(a.dns + pr * 8 + a.r * (wp / 16) + 2 * j);
-}
-
-template <int NF>
-__device__ __forceinline__ void load_nv_w(NvW& w, const uint8_t* wc, const uint8_t* ws, int n0, int N, int K,
-                                          int ks) {
-  static_assert(NF == 8, "one weight row per thread");
-  const int p = ks >> 2, j = ks & 3, wp = min(128, K - 128 * p);
-  const int64_t pn = (int64_t)p * N;
-  const int n = min(n0 + (int)threadIdx.x, N - 1);
-  w.codes = *reinterpret_cast<const uint4*>(wc + pn * 64 + (int64_t)n * (wp / 2) + 16 * j);
-  w.sc = ws[pn * 4 + (int64_t)n * (wp / 32) + j];
-}
-
-// Dequantize this thread's weight row (32 values) into the LDS tile as bf16.
-__device__ __forceinline__ void store_nv_w(const NvW& w, uint8_t* lds) {
-  const int row = threadIdx.x;
-  const float d = e4m3_value(w.sc);
-  const uint32_t c[4] = {w.codes.x, w.codes.y, w.codes.z, w.codes.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    *reinterpret_cast<uint4*>(lds + row * 64 + 16 * (q ^ swz_nv(row))) = dequant8_bf16(c[q], d);
-}
-
-template <int PAT, int NF>
-__device__ __forceinline__ void step_nv(v16f (&acc)[NF], const NvA& a, const uint8_t* lw, int lane) {
-  const int half = lane >> 5, col = lane & 31;
-  const uint4 sp = expand_block<PAT>(a.spc, a.spm);
-  const float dsp = e4m3_value(a.ssc & 0xFFu);
-  const float d0 = e4m3_value(a.dsc & 0xFFu), d1 = e4m3_value((a.dsc >> 8) & 0xFFu);
-  const uint32_t spw[4] = {sp.x, sp.y, sp.z, sp.w};
-  const uint32_t dnw[4] = {a.dn.x, a.dn.y, a.dn.z, a.dn.w};
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    // K values 8 half + 16 t + 0..7: dword (half + 2 t) of the block; the
-    // residual's 16-half is t
-    const bf16x8 asp = as_bf16x8(dequant8_bf16(spw[half + 2 * t], dsp));
-    const bf16x8 adn = as_bf16x8(dequant8_bf16(dnw[half + 2 * t], t ? d1 : d0));
-    bf16x8 b[NF];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const int row = f * 32 + col;
-      b[f] = as_bf16x8(*reinterpret_cast<const uint4*>(lw + row * 64 + 16 * ((half + 2 * t) ^ swz_nv(row))));
-    }
-#pragma unroll
-    for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(asp, b[f], acc[f], 0, 0, 0);
-#pragma unroll
-    for (int f = 0; f < NF; ++f) acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(adn, b[f], acc[f], 0, 0, 0);
-  }
-}
-
-template <int NF, int PAT, typename OutT>
-__global__ __launch_bounds__(256) void k_linear_nv(const uint8_t* sp_codes, const uint8_t* sp_meta,
-                                                   const uint8_t* sp_scale, const uint8_t* dn_codes,
-                                                   const uint8_t* dn_scale, const float* ts_x, int64_t M,
-                                                   const uint8_t* wc, const uint8_t* ws, const float* ts_w, int N,
-                                                   int K, OutT* Y, int64_t ldy, int gx, int gy) {
-  constexpr int BN = 32 * NF;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * BN * 64];
-  int mt, nt;
-  tile_of(blockIdx.x, gx, gy, mt, nt);
-  const int n0 = nt * BN;
-  const int64_t row_lo = (int64_t)mt * kBM;
-  const int64_t row_hi = row_lo + kBM < M ? row_lo + kBM : M;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5;
-  const int nks = K / 32;
-
-  int64_t orow = row_lo + wave * 32 + (lane & 31);
-  if (orow >= row_hi) orow = row_hi - 1;
-  ARow a;
-  a.r = orow;
-  a.R = M;
-  a.dn = dn_codes;
-  a.spc = sp_codes;
-  a.spm = sp_meta;
-  a.dns = dn_scale;
-  a.sps = sp_scale;
-
-  v16f acc[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[f][r] = 0.0f;
-
-  NvA a0, a1;
-  NvW wn;
-  const int last = nks - 1;
-  load_nv_w<NF>(wn, wc, ws, n0, N, K, 0);
-  load_nv_a(a0, a, 0, K);
-  store_nv_w(wn, lds);
-  load_nv_w<NF>(wn, wc, ws, n0, N, K, min(1, last));
-  load_nv_a(a1, a, min(1, last), K);
-  int ks = 0;
-  for (; ks + 1 < nks; ks += 2) {
-    __syncthreads();
-    step_nv<PAT, NF>(acc, a0, lds, lane);
-    store_nv_w(wn, lds + BN * 64);
-    load_nv_w<NF>(wn, wc, ws, n0, N, K, min(ks + 2, last));
-    load_nv_a(a0, a, min(ks + 2, last), K);
-    __syncthreads();
-    step_nv<PAT, NF>(acc, a1, lds + BN * 64, lane);
-    store_nv_w(wn, lds);
-    load_nv_w<NF>(wn, wc, ws, n0, N, K, min(ks + 3, last));
-    load_nv_a(a1, a, min(ks + 3, last), K);
-  }
-  if (ks < nks) {
-    __syncthreads();
-    step_nv<PAT, NF>(acc, a0, lds, lane);
-  }
-
-  const float scale = *ts_x * *ts_w;
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    const int col = n0 + f * 32 + (lane & 31);
-    if (col >= N) continue;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t row = row_lo + wave * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-      if (row < row_hi) store_out<OutT>(Y + row * ldy + col, acc[f][r] * scale);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Interleaved NVFP4 main loop (K a multiple of 128)
-// ---------------------------------------------------------------------------
-//
-// The same slot schedule as the MXFP4 loop, on v_mfma_f32_32x32x16_f16 with
-// the weight as first operand (each lane then owns an output row).  One K
-// step is one 32-position block: two 16-position MFMA sub-steps t, where lane
-// half h supplies positions 16 h + 8 t + 0..7 -- so a lane needs only its
-// half of each block (one residual scale, 8 bytes of residual codes, half the
-// backbone).  Between the step's 32 MFMAs run the weight reads of sub-step 1,
-// the fp16 dequantization of the next step's activations, the dequantization
-// and LDS store of the weight two steps ahead (three LDS stages) and the
-// reads of the next step's first weight operands.
-
-struct NvRaw {          // this lane's raw activation data of one step
-  uint2 dn;             // residual codes of positions 16 h + 0..15
-  uint32_t spc;         // compressed backbone codes of the same 16 positions;
-                        // from the dense backbone copy (PAT 0): their first 8 codes
-  uint32_t spm;         // their metadata (low 16 bits); PAT 0: the last 8 codes
-  uint32_t ssc, dsc;    // backbone and residual E4M3 scales (bytes)
-};
-
-struct NvOps {          // MFMA-ready fp16 operands of one step
-  uint4 sp[2], dn[2];
-};
-
-struct NvWRaw {         // one weight row of one step
-  uint4 codes;
-  uint32_t sc;
-};
-
-constexpr int kNvStage = 256 * 64;   // fp16 weight tile of one step: 256 rows x 32 positions
-
-// PAT 0: a.spc is the dense backbone copy (16 bytes per block, block-major).
-template <int PAT>
-__device__ __forceinline__ void nv_load_a(NvRaw& s, const ARow& a, int ks, int half) {
-  const int64_t V = ((int64_t)(ks >> 2) * a.R + a.r) * 4 + (ks & 3);   // block-major index
-  s.dn = *reinterpret_cast<const uint2*>(a.dn + V * 16 + 8 * half);
-  if (PAT == 0) {
-    const uint2 c = *reinterpret_cast<const uint2*>(a.spc + V * 16 + 8 * half);
-    s.spc = c.x;
-    s.spm = c.y;
-  } else {
-    s.spc = *reinterpret_cast<const uint32_t*>(a.spc + V * 8 + 4 * half);
-    s.spm = (uint32_t)*reinterpret_cast<const uint16_t*>(a.spm + V * 4 + 2 * half);
-  }
-  s.ssc = a.sps[V];
-  s.dsc = a.dns[V * 2 + half];
-}
-
-// Dense backbone codes D (0: positions 16 h + 0..7, 1: + 8..15) of a step:
-// read as they are from the dense copy, or expanded from the compressed form.
-template <int PAT, int D>
-__device__ __forceinline__ uint32_t nv_backbone_dw(const NvRaw& r) {
-  if (PAT == 0) return D == 0 ? r.spc : r.spm;
-  return expand_dw<PAT, D>(make_uint2(r.spc, 0u), r.spm);
-}
-
-__device__ __forceinline__ void nv_load_w(NvWRaw& w, const uint8_t* wc, const uint8_t* ws, int n0, int N, int ks) {
-  const int n = min(n0 + (int)threadIdx.x, N - 1);
-  const int64_t V = ((int64_t)(ks >> 2) * N + n) * 4 + (ks & 3);
-  w.codes = *reinterpret_cast<const uint4*>(wc + V * 16);
-  w.sc = ws[V];
-}
-
-template <int SUB, int F0, int F1>
-__device__ __forceinline__ void nv_read_b(uint4 (&b)[8], const uint8_t* lw, int lane) {
-  const int half = lane >> 5, col = lane & 31;
-#pragma unroll
-  for (int f = F0; f < F1; ++f) {
-    const int row = f * 32 + col;
-    b[f] = *reinterpret_cast<const uint4*>(lw + row * 64 + 16 * ((2 * half + SUB) ^ swz_nv(row)));
-  }
-}
-
-template <int SUB, int F>
-__device__ __forceinline__ void nv_mma(v16f (&acc)[8], const uint4& a, const uint4 (&b)[8]) {
-  acc[F] = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(b[F]), as_f16x8(a), acc[F], 0, 0, 0);
-}
-
-template <int PAT, class Issue>
-__device__ __forceinline__ void nv_step(v16f (&acc)[8], const NvOps& ops, uint4 (&b0)[8], const uint8_t* cur,
-                                        const uint8_t* nxt, uint8_t* wr, NvOps& opsn, const NvRaw& raw,
-                                        const NvWRaw& wst, int lane, Issue issue) {
-  const int tid = threadIdx.x;
-  uint4 b1[8];
-  issue();
-  SHARQ_FENCE();
-  // next step's activations: backbone expanded to 16 codes, then dequantized
-  // (their scales decoded behind the first two MFMAs)
-  f16x2 dsp, ddn;
-  uint32_t e0 = 0u, e1 = 0u;
-  // ---- sub-step 0, backbone
-  nv_mma<0, 0>(acc, ops.sp[0], b0); nv_read_b<1, 0, 1>(b1, cur, lane); dsp = nv_scale2(raw.ssc); SHARQ_FENCE();
-  nv_mma<0, 1>(acc, ops.sp[0], b0); nv_read_b<1, 1, 2>(b1, cur, lane); ddn = nv_scale2(raw.dsc);
-  e0 = nv_backbone_dw<PAT, 0>(raw); SHARQ_FENCE();
-  nv_mma<0, 2>(acc, ops.sp[0], b0); nv_read_b<1, 2, 3>(b1, cur, lane); SHARQ_FENCE();
-  nv_mma<0, 3>(acc, ops.sp[0], b0); nv_read_b<1, 3, 4>(b1, cur, lane); e1 = nv_backbone_dw<PAT, 1>(raw); SHARQ_FENCE();
-  nv_mma<0, 4>(acc, ops.sp[0], b0); nv_read_b<1, 4, 5>(b1, cur, lane);
-  opsn.sp[0].x = f16_pair<0>(e0, dsp); opsn.sp[0].y = f16_pair<1>(e0, dsp); SHARQ_FENCE();
-  nv_mma<0, 5>(acc, ops.sp[0], b0); nv_read_b<1, 5, 6>(b1, cur, lane);
-  opsn.sp[0].z = f16_pair<2>(e0, dsp); opsn.sp[0].w = f16_pair<3>(e0, dsp); SHARQ_FENCE();
-  nv_mma<0, 6>(acc, ops.sp[0], b0); nv_read_b<1, 6, 7>(b1, cur, lane);
-  opsn.sp[1].x = f16_pair<0>(e1, dsp); opsn.sp[1].y = f16_pair<1>(e1, dsp); SHARQ_FENCE();
-  nv_mma<0, 7>(acc, ops.sp[0], b0); nv_read_b<1, 7, 8>(b1, cur, lane);
-  opsn.sp[1].z = f16_pair<2>(e1, dsp); opsn.sp[1].w = f16_pair<3>(e1, dsp); SHARQ_FENCE();
-  // ---- sub-step 0, residual
-  nv_mma<0, 0>(acc, ops.dn[0], b0);
-  opsn.dn[0].x = f16_pair<0>(raw.dn.x, ddn); opsn.dn[0].y = f16_pair<1>(raw.dn.x, ddn); SHARQ_FENCE();
-  nv_mma<0, 1>(acc, ops.dn[0], b0);
-  opsn.dn[0].z = f16_pair<2>(raw.dn.x, ddn); opsn.dn[0].w = f16_pair<3>(raw.dn.x, ddn); SHARQ_FENCE();
-  nv_mma<0, 2>(acc, ops.dn[0], b0);
-  opsn.dn[1].x = f16_pair<0>(raw.dn.y, ddn); opsn.dn[1].y = f16_pair<1>(raw.dn.y, ddn); SHARQ_FENCE();
-  nv_mma<0, 3>(acc, ops.dn[0], b0);
-  opsn.dn[1].z = f16_pair<2>(raw.dn.y, ddn); opsn.dn[1].w = f16_pair<3>(raw.dn.y, ddn); SHARQ_FENCE();
-  // the weight row two steps ahead: dequantized into the other stage, each
-  // 16-byte part over two slots (4 values per slot)
-  const f16x2 dw = nv_scale2(wst.sc);
-  const int wrow = tid;
-  uint32_t wx, wy;
-  nv_mma<0, 4>(acc, ops.dn[0], b0);
-  wx = f16_pair<0>(wst.codes.x, dw); wy = f16_pair<1>(wst.codes.x, dw); SHARQ_FENCE();
-  nv_mma<0, 5>(acc, ops.dn[0], b0);
-  *reinterpret_cast<uint4*>(wr + wrow * 64 + 16 * (0 ^ swz_nv(wrow))) =
-      make_uint4(wx, wy, f16_pair<2>(wst.codes.x, dw), f16_pair<3>(wst.codes.x, dw));
-  SHARQ_FENCE();
-  nv_mma<0, 6>(acc, ops.dn[0], b0);
-  wx = f16_pair<0>(wst.codes.y, dw); wy = f16_pair<1>(wst.codes.y, dw); SHARQ_FENCE();
-  nv_mma<0, 7>(acc, ops.dn[0], b0);
-  *reinterpret_cast<uint4*>(wr + wrow * 64 + 16 * (1 ^ swz_nv(wrow))) =
-      make_uint4(wx, wy, f16_pair<2>(wst.codes.y, dw), f16_pair<3>(wst.codes.y, dw));
-  SHARQ_FENCE();
-  // ---- sub-step 1, backbone
-  nv_mma<1, 0>(acc, ops.sp[1], b1);
-  wx = f16_pair<0>(wst.codes.z, dw); wy = f16_pair<1>(wst.codes.z, dw); SHARQ_FENCE();
-  nv_mma<1, 1>(acc, ops.sp[1], b1);
-  *reinterpret_cast<uint4*>(wr + wrow * 64 + 16 * (2 ^ swz_nv(wrow))) =
-      make_uint4(wx, wy, f16_pair<2>(wst.codes.z, dw), f16_pair<3>(wst.codes.z, dw));
-  SHARQ_FENCE();
-  nv_mma<1, 2>(acc, ops.sp[1], b1);
-  wx = f16_pair<0>(wst.codes.w, dw); wy = f16_pair<1>(wst.codes.w, dw); SHARQ_FENCE();
-  nv_mma<1, 3>(acc, ops.sp[1], b1);
-  *reinterpret_cast<uint4*>(wr + wrow * 64 + 16 * (3 ^ swz_nv(wrow))) =
-      make_uint4(wx, wy, f16_pair<2>(wst.codes.w, dw), f16_pair<3>(wst.codes.w, dw));
-  SHARQ_FENCE();
-  nv_mma<1, 4>(acc, ops.sp[1], b1); SHARQ_FENCE();
-  nv_mma<1, 5>(acc, ops.sp[1], b1); SHARQ_FENCE();
-  nv_mma<1, 6>(acc, ops.sp[1], b1); SHARQ_FENCE();
-  nv_mma<1, 7>(acc, ops.sp[1], b1); SHARQ_FENCE();
-  // ---- sub-step 1, residual; the next step's first weight operands
-  nv_mma<1, 0>(acc, ops.dn[1], b1); nv_read_b<0, 0, 1>(b0, nxt, lane); SHARQ_FENCE();
-  nv_mma<1, 1>(acc, ops.dn[1], b1); nv_read_b<0, 1, 2>(b0, nxt, lane); SHARQ_FENCE();
-  nv_mma<1, 2>(acc, ops.dn[1], b1); nv_read_b<0, 2, 3>(b0, nxt, lane); SHARQ_FENCE();
-  nv_mma<1, 3>(acc, ops.dn[1], b1); nv_read_b<0, 3, 4>(b0, nxt, lane); SHARQ_FENCE();
-  nv_mma<1, 4>(acc, ops.dn[1], b1); nv_read_b<0, 4, 5>(b0, nxt, lane); SHARQ_FENCE();
-  nv_mma<1, 5>(acc, ops.dn[1], b1); nv_read_b<0, 5, 6>(b0, nxt, lane); SHARQ_FENCE();
-  nv_mma<1, 6>(acc, ops.dn[1], b1); nv_read_b<0, 6, 7>(b0, nxt, lane); SHARQ_FENCE();
-  nv_mma<1, 7>(acc, ops.dn[1], b1); nv_read_b<0, 7, 8>(b0, nxt, lane); SHARQ_FENCE();
-}
-
-template <int PAT>
-__device__ __forceinline__ void nv_ops_from_raw(NvOps& o, const NvRaw& r) {
-  const f16x2 dsp = nv_scale2(r.ssc), ddn = nv_scale2(r.dsc);
-  const uint32_t e0 = nv_backbone_dw<PAT, 0>(r), e1 = nv_backbone_dw<PAT, 1>(r);
-  o.sp[0] = make_uint4(f16_pair<0>(e0, dsp), f16_pair<1>(e0, dsp), f16_pair<2>(e0, dsp), f16_pair<3>(e0, dsp));
-  o.sp[1] = make_uint4(f16_pair<0>(e1, dsp), f16_pair<1>(e1, dsp), f16_pair<2>(e1, dsp), f16_pair<3>(e1, dsp));
-  o.dn[0] = make_uint4(f16_pair<0>(r.dn.x, ddn), f16_pair<1>(r.dn.x, ddn), f16_pair<2>(r.dn.x, ddn),
-                       f16_pair<3>(r.dn.x, ddn));
-  o.dn[1] = make_uint4(f16_pair<0>(r.dn.y, ddn), f16_pair<1>(r.dn.y, ddn), f16_pair<2>(r.dn.y, ddn),
-                       f16_pair<3>(r.dn.y, ddn));
-}
-
-__device__ __forceinline__ void nv_store_w(const NvWRaw& w, uint8_t* stage) {
-  const int row = threadIdx.x;
-  const f16x2 d = nv_scale2(w.sc);
-  const uint32_t c[4] = {w.codes.x, w.codes.y, w.codes.z, w.codes.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    *reinterpret_cast<uint4*>(stage + row * 64 + 16 * (q ^ swz_nv(row))) =
-        make_uint4(f16_pair<0>(c[q], d), f16_pair<1>(c[q], d), f16_pair<2>(c[q], d), f16_pair<3>(c[q], d));
-}
-
-template <int PAT, typename OutT>
-__device__ __forceinline__ void tile_nv_il(const uint8_t* sp_codes, const uint8_t* sp_meta,
-                                           const uint8_t* sp_scale, const uint8_t* dn_codes,
-                                           const uint8_t* dn_scale, const float* ts_x, int64_t M,
-                                           const uint8_t* wc, const uint8_t* ws, const float* ts_w, int N, int K,
-                                           OutT* Y, int64_t ldy, int mt, int nt, uint8_t* lds) {
-  constexpr int NF = 8;
-  const int n0 = nt * 256;
-  const int64_t row_lo = (int64_t)mt * kBM;
-  const int64_t row_hi = row_lo + kBM < M ? row_lo + kBM : M;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5;
-  const int nks = K / 32;   // one step per 32-position block
-
-  int64_t orow = row_lo + wave * 32 + (lane & 31);
-  if (orow >= row_hi) orow = row_hi - 1;   // clamp: loads stay in bounds, stores are masked
-  ARow a;
-  a.r = orow;
-  a.R = M;
-  a.dn = dn_codes;
-  a.spc = sp_codes;
-  a.spm = sp_meta;
-  a.dns = dn_scale;
-  a.sps = sp_scale;
-
-  v16f acc[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[f][r] = 0.0f;
-
-  // invariant at step k (sets by k mod 2, stages by k mod 3): stages k, k+1
-  // hold W(k), W(k+1); b0 = step k's first operands; o[k] ready;
-  // r[k+1] = raw A(k+1); w[k] = raw W(k+2)
-  const int last = nks - 1;
-  const auto cl = [&](int k) { return k < last ? k : last; };
-  NvRaw r0, r1;
-  NvWRaw w0, w1;
-  NvOps o0, o1;
-  uint4 b0[8];
-  uint8_t* st0 = lds;
-  uint8_t* st1 = lds + kNvStage;
-  uint8_t* st2 = lds + 2 * kNvStage;
-  nv_load_w(w0, wc, ws, n0, N, 0);
-  nv_load_w(w1, wc, ws, n0, N, cl(1));
-  nv_load_a<PAT>(r0, a, 0, half);
-  nv_load_a<PAT>(r1, a, cl(1), half);
-  nv_store_w(w0, st0);
-  nv_store_w(w1, st1);
-  nv_ops_from_raw<PAT>(o0, r0);
-  nv_load_w(w0, wc, ws, n0, N, cl(2));
-  __syncthreads();
-  nv_read_b<0, 0, 8>(b0, st0, lane);
-
-  int ks = 0;
-  for (; ks + 1 < nks; ks += 2) {
-    nv_step<PAT>(acc, o0, b0, st0, st1, st2, o1, r1, w0, lane, [&] {
-      nv_load_w(w1, wc, ws, n0, N, cl(ks + 3));
-      nv_load_a<PAT>(r0, a, cl(ks + 2), half);
-    });
-    __syncthreads();
-    nv_step<PAT>(acc, o1, b0, st1, st2, st0, o0, r0, w1, lane, [&] {
-      nv_load_w(w0, wc, ws, n0, N, cl(ks + 4));
-      nv_load_a<PAT>(r1, a, cl(ks + 3), half);
-    });
-    __syncthreads();
-    uint8_t* t = st0;   // rotate the stages by two
-    st0 = st2;
-    st2 = st1;
-    st1 = t;
-  }
-  if (ks < nks) nv_step<PAT>(acc, o0, b0, st0, st1, st2, o1, r1, w0, lane, [] {});
-
-  const float scale = *ts_x * *ts_w;
-  const int64_t row = row_lo + wave * 32 + (lane & 31);
-  if (row >= row_hi) return;
-  OutT* yr = Y + row * ldy;
-  const bool vec = ((reinterpret_cast<uintptr_t>(Y) | (uintptr_t)(ldy * (int64_t)sizeof(OutT))) &
-                    (uintptr_t)(Vec4Out<OutT>::kAlign - 1)) == 0;
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col = n0 + f * 32 + 8 * g + 4 * half;
-      const float v0 = acc[f][4 * g] * scale, v1 = acc[f][4 * g + 1] * scale;
-      const float v2 = acc[f][4 * g + 2] * scale, v3 = acc[f][4 * g + 3] * scale;
-      if (vec && col + 3 < N) {
-        Vec4Out<OutT>::put(yr + col, v0, v1, v2, v3);
-      } else {
-        if (col < N) store_out<OutT>(yr + col, v0);
-        if (col + 1 < N) store_out<OutT>(yr + col + 1, v1);
-        if (col + 2 < N) store_out<OutT>(yr + col + 2, v2);
-        if (col + 3 < N) store_out<OutT>(yr + col + 3, v3);
-      }
-    }
-  }
-}
-
-static int device_cus();   // compute units of the current device (host launchers below)
-
-// The small-M kernel of the formats on 16-bit MFMA (sharq_skinny16.hip).
-bool use_skinny16(bool nv, int64_t M, int N, int K);
-hipError_t launch_linear_skinny16(bool nv, int pat, int ydt, const uint8_t* spc, const uint8_t* spm,
-                                  const uint8_t* sps, const uint8_t* dnc, const uint8_t* dns, const float* tsx,
-                                  int64_t M, const uint8_t* wc, const uint8_t* ws, const float* tsw, int N, int K,
-                                  void* Y, int64_t ldy, hipStream_t st);
-
-// Persistent: at most one workgroup per CU walks the tiles b, b + G, ... in
-// the XCD-aware order of tile_at (any grid: the Qwen2.5-7B shapes have 148
-// and 14 column tiles; measured neutral there, where the dequantization and
-// MFMA work bound the kernel).
-template <int PAT, typename OutT>
-__global__ __launch_bounds__(256) void k_linear_nv_il(const uint8_t* sp_codes, const uint8_t* sp_meta,
-                                                      const uint8_t* sp_scale, const uint8_t* dn_codes,
-                                                      const uint8_t* dn_scale, const float* ts_x, int64_t M,
-                                                      const uint8_t* wc, const uint8_t* ws, const float* ts_w, int N,
-                                                      int K, OutT* Y, int64_t ldy, int gx, int gy) {
-  __shared__ __attribute__((aligned(16))) uint8_t lds[3 * kNvStage];
-  const int ids = 8 * ((gx * gy + 7) >> 3);
-  for (int id = (int)blockIdx.x; id < ids; id += (int)gridDim.x) {
-    int mt, nt;
-    if (!tile_at(id, gx, gy, mt, nt)) continue;   // uniform across the workgroup
-    tile_nv_il<PAT, OutT>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, ts_x, M, wc, ws, ts_w, N, K, Y, ldy, mt, nt,
-                          lds);
-    __syncthreads();   // the LDS stages are free before the next tile's prologue
-  }
-}
-
-template <int PAT, typename OutT>
-static hipError_t go_nv(const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
-                        const uint8_t* dns, const float* tsx, int64_t M, const uint8_t* wc, const uint8_t* ws,
-                        const float* tsw, int N, int K, void* Y, int64_t ldy, hipStream_t st) {
-  constexpr int NF = 8;
-  const int gx = (N + 32 * NF - 1) / (32 * NF), gy = (int)((M + kBM - 1) / kBM);
-  if (K % kBK == 0) {
-    const int tiles = gx * gy, cus = device_cus();
-    k_linear_nv_il<PAT, OutT><<<dim3((unsigned)(tiles < cus ? tiles : cus)), dim3(256), 0, st>>>(
-        spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, reinterpret_cast<OutT*>(Y), ldy, gx, gy);
-    return hipGetLastError();
-  }
-  if constexpr (PAT == 0) {
-    return hipErrorInvalidValue;   // the dense backbone copy needs K a multiple of 128
-  } else {
-    k_linear_nv<NF, PAT, OutT><<<dim3((unsigned)(gx * gy)), dim3(256), 0, st>>>(
-        spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, reinterpret_cast<OutT*>(Y), ldy, gx, gy);
-    return hipGetLastError();
-  }
-}
-
-template <int PAT>
-static hipError_t go_nv_dt(int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
-                           const uint8_t* dns, const float* tsx, int64_t M, const uint8_t* wc, const uint8_t* ws,
-                           const float* tsw, int N, int K, void* Y, int64_t ldy, hipStream_t st) {
-  if (ydt == 2) return go_nv<PAT, float>(spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);
-  if (ydt == 1) return go_nv<PAT, _Float16>(spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);
-  return go_nv<PAT, uint16_t>(spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);
-}
-
-hipError_t launch_linear_nv(int pat, int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps,
-                            const uint8_t* dnc, const uint8_t* dns, const float* tsx, int64_t M, const uint8_t* wc,
-                            const uint8_t* ws, const float* tsw, int N, int K, void* Y, int64_t ldy,
-                            const uint8_t* spd, hipStream_t st) {
-  const bool dense = spd && K % kBK == 0;
-  if ((dense || spc != nullptr) && use_skinny16(true, M, N, K))
-    return launch_linear_skinny16(true, dense ? 0 : pat, ydt, dense ? spd : spc, spm, sps, dnc, dns, tsx, M, wc, ws,
-                                  tsw, N, K, Y, ldy, st);
-  if (dense) return go_nv_dt<0>(ydt, spd, nullptr, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);
-  if (spc == nullptr) return hipErrorInvalidValue;   // rejected by the C ABI (K not a multiple of 128)
-  return pat == 24 ? go_nv_dt<24>(ydt, spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st)
-                   : go_nv_dt<48>(ydt, spc, spm, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);
-}
-
-// ---------------------------------------------------------------------------
 // Path combinations (Sec. 4.4, table "ablation-combination"): the sum of up
 // to two paths, each sparse (compressed codes + metadata, expanded in
 // registers; scale per 32 logical positions) or dense (plain codes), into one
@@ -2504,6 +1756,18 @@ __global__ __launch_bounds__(256) void k_linear_slots_nv(SlotBuf p1, SlotBuf p2,
   }
 }
 
+// The small-M kernel of the formats on 16-bit MFMA (sharq_skinny16.hip).
+bool use_skinny16(bool nv, int64_t M, int N, int K);
+hipError_t launch_linear_skinny16(bool nv, int pat, int ydt, const uint8_t* spc, const uint8_t* spm,
+                                  const uint8_t* sps, const uint8_t* dnc, const uint8_t* dns, const float* tsx,
+                                  int64_t M, const uint8_t* wc, const uint8_t* ws, const float* tsw, int N, int K,
+                                  void* Y, int64_t ldy, hipStream_t st);
+
+// HiF4 with K a multiple of 128 (sharq_linear16.hip).
+hipError_t launch_linear16_hif4(int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps,
+                                const uint8_t* dnc, const uint8_t* dns, int64_t M, const uint8_t* wc,
+                                const uint8_t* ws, int N, int K, void* Y, int64_t ldy, hipStream_t st);
+
 // ---------------------------------------------------------------------------
 // HiF4 two-path GEMM (2:4 backbone + dense residual).  No matrix instruction
 // takes HiF4, but every HiF4 value E6M2 * 2^(E1_8 + E1_16) * S1P2 has at most
@@ -2667,36 +1931,6 @@ __global__ __launch_bounds__(256) void k_linear_hif4(const uint8_t* sp_codes, co
 // Host-side launchers
 // ---------------------------------------------------------------------------
 
-// Compute units of the current device (queried once per device).
-static int device_cus() {
-  static int cache[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cache[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    cache[dev] = n;
-  }
-  return cache[dev];
-}
-
-// Work units of the persistent kernel: whole tiles, with a last round that
-// would be at most half full run as twice as many half tiles.
-struct PersistPlan {
-  int grid, full, halves;
-};
-
-static PersistPlan persist_plan(int gx, int gy) {
-  const int tiles = gx * gy, cus = device_cus();
-  PersistPlan p{tiles < cus ? tiles : cus, tiles, 0};
-  const int r = tiles % p.grid;
-  if (tiles > p.grid && r > 0 && 2 * r <= p.grid) {
-    p.full = tiles - r;
-    p.halves = 2 * r;
-  }
-  return p;
-}
-
 template <int NF, int PAT, bool SDW, typename OutT>
 static hipError_t go_linear(const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
                             const uint8_t* dns, int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K,
@@ -2825,7 +2059,6 @@ hipError_t launch_linear_mx_grouped(int pat, int ydt, const uint8_t* spc, const 
                                             st);
 }
 
-
 template <int K1, int K2, typename OutT>
 static hipError_t go_slots(bool nv, const SlotBuf& p1, const SlotBuf& p2, const float* tsx, int64_t M,
                            const uint8_t* wc, const uint8_t* ws, const float* tsw, int N, int K, void* Y, int64_t ldy,
@@ -2871,7 +2104,6 @@ hipError_t launch_linear_slots(int mode, int pat, int ydt, bool nv, const uint8_
   }
 }
 
-
 // HiF4 (2:4 backbone, K a multiple of 64).
 hipError_t launch_linear_hif4(int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
                               const uint8_t* dns, int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K,
@@ -2879,6 +2111,7 @@ hipError_t launch_linear_hif4(int ydt, const uint8_t* spc, const uint8_t* spm, c
   if (use_skinny16(false, M, N, K))
     return launch_linear_skinny16(false, 24, ydt, spc, spm, sps, dnc, dns, nullptr, M, wc, ws, nullptr, N, K, Y, ldy,
                                   st);
+  if (K % kBK == 0) return launch_linear16_hif4(ydt, spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
   const int gx = (N + 255) / 256, gy = (int)((M + kBM - 1) / kBM);
   const dim3 grid((unsigned)(gx * gy)), block(256);
   if (ydt == 2)
