@@ -36,7 +36,6 @@ namespace sharq {
 
 constexpr int kLdsStride = 80;    // bytes per staged weight row (64 + 16 to spread LDS banks)
 constexpr int kSkinnyMaxM = 32;   // activation rows up to which the small-M kernel runs
-constexpr int kSkinnyMaxRowTiled = 256;   // ... and, when the main kernel has few tiles, up to this many
 
 __device__ __forceinline__ v8i as_operand(uint4 q) {
   v8i v;
@@ -308,7 +307,7 @@ __device__ __forceinline__ void tile_mx(const uint8_t* sp_codes, const uint8_t* 
 }
 
 // ---------------------------------------------------------------------------
-// Interleaved main loop (K a multiple of 128, 256 output columns)
+// Interleaved main loop (full 128-wide panels, 256 output columns)
 // ---------------------------------------------------------------------------
 //
 // With one wavefront per SIMD the matrix core idles whenever the wavefront
@@ -863,9 +862,48 @@ __device__ __forceinline__ int64_t il_row(const int32_t* row_index, int64_t row_
   return row_index ? (int64_t)row_index[orow] : orow;
 }
 
+// The last panel of a K that is not a multiple of 128 (1 to 3 blocks), after
+// the tile's full panels: its few operands come straight from global memory,
+// block 2 SUB + half per lane; lanes past K reread block 0 and zero the weight.
+// Beside ~30 full steps its latency is small (about one step), and the full
+// panels keep the interleaved pipeline: M 1024, N 5000, K 2080, 50 us on the
+// double-buffered kernel that handled such K before.
+template <int PAT, int NF>
+__device__ __forceinline__ void il_tail(v16f (&acc)[NF], const ARow& a, const uint8_t* wc, const uint8_t* ws, int n0,
+                                        int N, int K, int lane, int half) {
+  const int ks = K / kBK, nb = (K - kBK * ks) >> 5, col = lane & 31;
+  const int64_t pr = (int64_t)ks * a.R * 4 + a.r * nb, pn = (int64_t)ks * N * 4;
+#pragma unroll
+  for (int sub = 0; sub < 2; ++sub) {
+    if (2 * sub >= nb) break;   // the same in every lane
+    const bool in = 2 * sub + half < nb;
+    const int j = in ? 2 * sub + half : 0;
+    const uint4 dn = *reinterpret_cast<const uint4*>(a.dn + (pr + j) * 16);
+    const uint2 c = *reinterpret_cast<const uint2*>(a.spc + (pr + j) * 8);
+    const uint32_t meta = *reinterpret_cast<const uint32_t*>(a.spm + (pr + j) * 4);
+    const uint32_t ssp = a.sps[pr + j], sdn = a.dns[pr + j];
+    uint4 b[NF];
+    uint32_t sw[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const int64_t V = pn + (int64_t)min(n0 + 32 * f + col, N - 1) * nb + j;
+      b[f] = *reinterpret_cast<const uint4*>(wc + V * 16);
+      sw[f] = ws[V];
+    }
+    const v8i sp = as_operand(expand_block<PAT>(c, meta)), rs = as_operand(dn);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      if (!in) b[f] = make_uint4(0u, 0u, 0u, 0u);
+      acc[f] = mfma_fp4<0, 0>(as_operand(b[f]), sp, acc[f], sw[f], ssp);
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[f] = mfma_fp4<0, 0>(as_operand(b[f]), rs, acc[f], sw[f], sdn);
+  }
+}
+
 // One tile of the interleaved pipeline, alone: its LDS stages at lds, its
 // epilogue staged over them once every wavefront is done with them.
-template <int PAT, typename OutT, int NF>
+template <int PAT, typename OutT, int NF, bool TAIL = false>
 __device__ __forceinline__ void tile_mx_il(const uint8_t* sp_codes, const uint8_t* sp_meta, const uint8_t* sp_scale,
                                            const uint8_t* dn_codes, const uint8_t* dn_scale, const int32_t* row_index,
                                            int64_t act_rows, int64_t row_lo, int64_t row_hi, const uint8_t* wc,
@@ -892,6 +930,7 @@ __device__ __forceinline__ void tile_mx_il(const uint8_t* sp_codes, const uint8_
   il_issue<PAT, NF>(p, a, wc, ws, n0, N, K, half);
   il_start<PAT, NF>(p, wc, ws, n0, N, K, lds, b0, bwa, lane, half);
   il_main<PAT, NF>(acc, p, b0, bwa, a, wc, ws, n0, N, K, lds, lane, half, lut);
+  if constexpr (TAIL) il_tail<PAT, NF>(acc, a, wc, ws, n0, N, K, lane, half);
   __syncthreads();   // every wavefront is done with the weight stages
   il_epilogue<OutT, NF>(acc, Y, ldy, row_lo, row_hi, n0, N, lds + wave * kEpiWave, wave, lane);
 }
@@ -910,7 +949,7 @@ struct IlTile {
 // issue order, so loads issued behind the stores would first wait for the
 // stores (64 KB per tile) to drain.  The epilogue therefore has its own LDS
 // region `epi` (4 kEpiWave bytes) beside the three stages at `lds`.
-template <int PAT, typename OutT, int SPR = 0, class Next>
+template <int PAT, typename OutT, bool TAIL, int SPR = 0, class Next>
 __device__ __forceinline__ void tiles_mx_il(const uint8_t* sp_codes, const uint8_t* sp_meta, const uint8_t* sp_scale,
                                             const uint8_t* dn_codes, const uint8_t* dn_scale, int64_t act_rows, int N,
                                             int K, OutT* Y, int64_t ldy, uint8_t* lds, uint8_t* epi,
@@ -940,6 +979,7 @@ __device__ __forceinline__ void tiles_mx_il(const uint8_t* sp_codes, const uint8
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[f][r] = 0.0f;
     il_main<PAT, 8, SPR>(acc, p, b0, bwa, a, t.wc, t.ws, t.n0, N, K, lds, lane, half, lut);
+    if constexpr (TAIL) il_tail<PAT, 8>(acc, a, t.wc, t.ws, t.n0, N, K, lane, half);
     if (more) {
       a.r = tn.r;
       il_issue<PAT, 8>(p, a, tn.wc, tn.ws, tn.n0, N, K, half);
@@ -951,8 +991,8 @@ __device__ __forceinline__ void tiles_mx_il(const uint8_t* sp_codes, const uint8
   }
 }
 
-// One tile per workgroup, for K not a multiple of 128 (the simpler pipeline
-// of tile_mx, which handles a narrow last panel).
+// One tile per workgroup, for K below 128 (the simpler pipeline of tile_mx,
+// which needs no full panel).
 template <int NF, int PAT, bool SCALE_DW, typename OutT>
 __global__ __launch_bounds__(256) void k_linear_mx(const uint8_t* sp_codes, const uint8_t* sp_meta,
                                                    const uint8_t* sp_scale, const uint8_t* dn_codes,
@@ -972,7 +1012,7 @@ __global__ __launch_bounds__(256) void k_linear_mx(const uint8_t* sp_codes, cons
                                    K, Y, ldy, lds_w, lds_s);
 }
 
-// Persistent dense kernel (K a multiple of 128): at most one workgroup per
+// Persistent dense kernel (K of at least 128): at most one workgroup per
 // CU, walking the work units b, b + G, b + 2G, ... (G workgroups).  A tile's
 // output stores then drain while the same CU starts its next tile instead of
 // the whole grid waiting at the end of every round (3% on the Llama gate/up
@@ -986,7 +1026,7 @@ __global__ __launch_bounds__(256) void k_linear_mx(const uint8_t* sp_codes, cons
 // Llama qkv shape: 384 tiles on 256 CUs).  Half tile u covers tile t(u),
 // columns 128 h(u) on; with r a multiple of 8, t(u) keeps the XCD of u.
 
-template <int PAT, typename OutT>
+template <int PAT, typename OutT, bool TAIL>
 __global__ __launch_bounds__(256) void k_linear_mx_persist(const uint8_t* sp_codes, const uint8_t* sp_meta,
                                                            const uint8_t* sp_scale, const uint8_t* dn_codes,
                                                            const uint8_t* dn_scale, int64_t M, const uint8_t* wc,
@@ -999,7 +1039,7 @@ __global__ __launch_bounds__(256) void k_linear_mx_persist(const uint8_t* sp_cod
     __syncthreads();
   }
   int id = (int)blockIdx.x;
-  tiles_mx_il<PAT, OutT>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, M, N, K, Y, ldy, lds,
+  tiles_mx_il<PAT, OutT, TAIL>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, M, N, K, Y, ldy, lds,
                          lds + 3 * kStageBytes, lut48, [&](IlTile& t) {
                            if (id >= full) return false;
                            int mt, nt;
@@ -1020,7 +1060,7 @@ __global__ __launch_bounds__(256) void k_linear_mx_persist(const uint8_t* sp_cod
     const int64_t m0 = (int64_t)mt * kBM;
     const int64_t m1 = m0 + kBM < M ? m0 + kBM : M;
     __syncthreads();   // the LDS stages are free before this tile's prologue
-    tile_mx_il<PAT, OutT, 4>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, nullptr, M, m0, m1, wc, ws,
+    tile_mx_il<PAT, OutT, 4, TAIL>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, nullptr, M, m0, m1, wc, ws,
                              nt * 256 + 128 * h, N, K, Y, ldy, lds, lut48);
   }
 }
@@ -1101,7 +1141,7 @@ __global__ __launch_bounds__(256) void k_linear_mx_grouped(
                                      wce, wse, n0, N, K, Y, ldy, lds_w, lds_s);
 }
 
-// Persistent grouped form (K a multiple of 128): at most one workgroup per
+// Persistent grouped form (K of at least 128): at most one workgroup per
 // CU walks the real (column tile, item) pairs -- their count comes from the
 // same on-device scan -- so a CU starts its next tile without a new
 // workgroup launch and the padding items of the launch-per-tile form cost
@@ -1116,7 +1156,7 @@ __global__ __launch_bounds__(256) void k_linear_mx_grouped(
 // units as 220 halves: 164.4 -> 162.8 us).  GATHER (a row map is given):
 // full tiles take the spread load schedule of step5 (gate_up 165 -> 154 us,
 // bit-identical; contiguous rows keep the burst, which is faster for them).
-template <int PAT, typename OutT, bool GATHER = false>
+template <int PAT, typename OutT, bool TAIL, bool GATHER>
 __global__ __launch_bounds__(256) void k_linear_mx_grouped_persist(
     const uint8_t* sp_codes, const uint8_t* sp_meta, const uint8_t* sp_scale, const uint8_t* dn_codes,
     const uint8_t* dn_scale, const int32_t* row_index, int64_t act_rows, const int32_t* offs, int E,
@@ -1172,7 +1212,7 @@ __global__ __launch_bounds__(256) void k_linear_mx_grouped_persist(
   // [x per, (x + 1) per); ids whose unit is past the last are skipped.
   const int per = (full + 7) >> 3;
   int id = (int)blockIdx.x;
-  tiles_mx_il<PAT, OutT, GATHER ? 1 : 0>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, act_rows, N, K, Y, ldy, lds,
+  tiles_mx_il<PAT, OutT, TAIL, GATHER ? 1 : 0>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, act_rows, N, K, Y, ldy, lds,
                          lds + 3 * kStageBytes, lut48, [&](IlTile& t) {
                            int u = full;
                            while (u >= full) {
@@ -1194,7 +1234,7 @@ __global__ __launch_bounds__(256) void k_linear_mx_grouped_persist(
     int64_t row_lo, row_hi;
     locate(u, e, row_lo, row_hi);
     __syncthreads();   // the LDS stages are free before this tile's prologue
-    tile_mx_il<PAT, OutT, 4>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, row_index, act_rows, row_lo, row_hi,
+    tile_mx_il<PAT, OutT, 4, TAIL>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, row_index, act_rows, row_lo, row_hi,
                              wc + (int64_t)e * N * (K / 2), ws + (int64_t)e * N * (K / 32), (u % gx) * 256 + 128 * h,
                              N, K, Y, ldy, lds, lut48);
   }
@@ -1229,42 +1269,55 @@ struct SkinnyStage {
   uint32_t sdn[MF], ssp[MF];
 };
 
+struct SkinnyArgs {
+  const uint8_t *spc, *spm, *sps, *dnc, *dns, *wc, *ws;
+  int64_t M;
+  int N, K;
+};
+
 // PAT 0: spc is the dense backbone copy (16 bytes per block, the residual
-// codes' layout) and spm is unused.
-template <int MF, int NB, int PAT>
-__device__ __forceinline__ void skinny_load(SkinnyStage<MF, NB>& st, const uint8_t* spc, const uint8_t* spm,
-                                            const uint8_t* sps, const uint8_t* dnc, const uint8_t* dns, int64_t M,
-                                            int64_t r0, const uint8_t* wc, const uint8_t* ws, int N, int n0, int ks,
+// codes' layout) and spm is unused.  RAG: K is not a multiple of 128; in the
+// narrower last panel, lanes whose block lies past K reread block 0 (and zero
+// its weight codes in skinny_step).
+template <int MF, int NB, int PAT, bool RAG>
+__device__ __forceinline__ void skinny_load(SkinnyStage<MF, NB>& st, const SkinnyArgs& p, int64_t r0, int n0, int ks,
                                             int lane) {
-  const int j = lane >> 4;   // block within the panel
-  const int64_t pn = (int64_t)ks * N, pm = (int64_t)ks * M;
+  const int nb = RAG ? min(128, p.K - 128 * ks) >> 5 : 4;   // blocks of this panel
+  const int j = RAG && (lane >> 4) >= nb ? 0 : lane >> 4;   // block within the panel
+  const int64_t pn = (int64_t)ks * p.N * 4, pm = (int64_t)ks * p.M * 4;   // blocks before it
 #pragma unroll
   for (int n = 0; n < NB; ++n) {
-    const int col = min(n0 + 16 * n + (lane & 15), N - 1);
-    st.w[n] = *reinterpret_cast<const uint4*>(wc + (pn + col) * 64 + 16 * j);
-    st.ws[n] = ws[(pn + col) * 4 + j];
+    const int64_t V = pn + (int64_t)min(n0 + 16 * n + (lane & 15), p.N - 1) * nb + j;
+    st.w[n] = *reinterpret_cast<const uint4*>(p.wc + V * 16);
+    st.ws[n] = p.ws[V];
   }
 #pragma unroll
   for (int m = 0; m < MF; ++m) {
     int64_t row = r0 + 16 * m + (lane & 15);
-    if (row >= M) row = M - 1;
-    const int64_t V = (pm + row) * 4 + j;   // block-major index of (row, block)
-    st.dn[m] = *reinterpret_cast<const uint4*>(dnc + V * 16);
+    if (row >= p.M) row = p.M - 1;
+    const int64_t V = pm + row * nb + j;   // block-major index of (row, block)
+    st.dn[m] = *reinterpret_cast<const uint4*>(p.dnc + V * 16);
     if (PAT == 0) {
-      st.spd[m] = *reinterpret_cast<const uint4*>(spc + V * 16);
+      st.spd[m] = *reinterpret_cast<const uint4*>(p.spc + V * 16);
     } else {
-      st.spc[m] = *reinterpret_cast<const uint2*>(spc + V * 8);
-      st.spm[m] = *reinterpret_cast<const uint32_t*>(spm + V * 4);
+      st.spc[m] = *reinterpret_cast<const uint2*>(p.spc + V * 8);
+      st.spm[m] = *reinterpret_cast<const uint32_t*>(p.spm + V * 4);
     }
-    st.sdn[m] = dns[V];
-    st.ssp[m] = sps[V];
+    st.sdn[m] = p.dns[V];
+    st.ssp[m] = p.sps[V];
   }
 }
 
 // The weight is the MFMA's first operand: accumulator element r of lane l is
 // then output column 4 (l / 16) + r of the fragment and activation row l % 16.
-template <int MF, int NB, int PAT>
-__device__ __forceinline__ void skinny_step(v4f_t (&acc)[MF][NB], const SkinnyStage<MF, NB>& st) {
+template <int MF, int NB, int PAT, bool RAG>
+__device__ __forceinline__ void skinny_step(v4f_t (&acc)[MF][NB], SkinnyStage<MF, NB>& st, int K, int ks, int lane) {
+  if (RAG) {
+    const uint32_t in = 32 * (lane >> 4) < K - 128 * ks ? ~0u : 0u;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+      st.w[n] = make_uint4(st.w[n].x & in, st.w[n].y & in, st.w[n].z & in, st.w[n].w & in);
+  }
 #pragma unroll
   for (int m = 0; m < MF; ++m) {
     const v8i asp = as_operand(PAT == 0 ? st.spd[m] : expand_block<PAT>(st.spc[m], st.spm[m]));
@@ -1297,19 +1350,16 @@ __device__ __forceinline__ void skinny_tile(int id, int ncg, int nrt, int& cg, i
   rt = idp - cg * nrt;
 }
 
-template <int MF, int NB, int KS, int PAT, typename OutT>
-__global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(const uint8_t* sp_codes, const uint8_t* sp_meta,
-                                                              const uint8_t* sp_scale, const uint8_t* dn_codes,
-                                                              const uint8_t* dn_scale, int64_t M, const uint8_t* wc,
-                                                              const uint8_t* ws, int N, int K, OutT* Y, int64_t ldy,
-                                                              int ncg, int nrt) {
-  __shared__ float part[KS - 1][MF * NB][64][4];
+template <int MF, int NB, int KS, int PAT, bool RAG>
+__global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(SkinnyArgs p, void* Y, int ydt, int64_t ldy, int ncg,
+                                                              int nrt) {
+  __shared__ float part[KS][MF * NB][256];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   int cg, rt;
   skinny_tile(blockIdx.x, ncg, nrt, cg, rt);
   const int n0 = cg * 16 * NB;
   const int64_t r0 = (int64_t)rt * 16 * MF;
-  const int nks = K / kBK;
+  const int nks = (p.K + kBK - 1) / kBK;
   const int per = (nks + KS - 1) / KS;
   const int k0 = wave * per, k1 = min(nks, k0 + per);
 
@@ -1320,61 +1370,51 @@ __global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(const uint8_t* sp_
     for (int n = 0; n < NB; ++n) acc[m][n] = v4f_t{0.0f, 0.0f, 0.0f, 0.0f};
 
   SkinnyStage<MF, NB> s0, s1;
-  if (k0 < k1)
-    skinny_load<MF, NB, PAT>(s0, sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, M, r0, wc, ws, N, n0, k0, lane);
-  if (k0 + 1 < k1)
-    skinny_load<MF, NB, PAT>(s1, sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, M, r0, wc, ws, N, n0, k0 + 1, lane);
+  if (k0 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, r0, n0, k0, lane);
+  if (k0 + 1 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, r0, n0, k0 + 1, lane);
   int ks = k0;
   for (; ks + 1 < k1; ks += 2) {
-    skinny_step<MF, NB, PAT>(acc, s0);
-    if (ks + 2 < k1)
-      skinny_load<MF, NB, PAT>(s0, sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, M, r0, wc, ws, N, n0, ks + 2, lane);
-    skinny_step<MF, NB, PAT>(acc, s1);
-    if (ks + 3 < k1)
-      skinny_load<MF, NB, PAT>(s1, sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, M, r0, wc, ws, N, n0, ks + 3, lane);
+    skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
+    if (ks + 2 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, r0, n0, ks + 2, lane);
+    skinny_step<MF, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
+    if (ks + 3 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, r0, n0, ks + 3, lane);
   }
-  if (ks < k1) skinny_step<MF, NB, PAT>(acc, s0);
+  if (ks < k1) skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
 
-  // partial tiles of wavefronts 1..KS-1 to LDS; wavefront 0 adds them in order
-  if (wave > 0) {
+  // the KS partial tiles, added by all threads in the order of K
 #pragma unroll
-    for (int m = 0; m < MF; ++m)
+  for (int m = 0; m < MF; ++m)
 #pragma unroll
-      for (int n = 0; n < NB; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) part[wave - 1][m * NB + n][lane][r] = acc[m][n][r];
-  }
+    for (int n = 0; n < NB; ++n) *reinterpret_cast<v4f_t*>(&part[wave][m * NB + n][4 * lane]) = acc[m][n];
   __syncthreads();
-  if (wave != 0) return;
-  for (int w = 0; w < KS - 1; ++w)
-#pragma unroll
-    for (int m = 0; m < MF; ++m)
-#pragma unroll
-      for (int n = 0; n < NB; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[m][n][r] += part[w][m * NB + n][lane][r];
-#pragma unroll
-  for (int m = 0; m < MF; ++m) {
-    const int64_t row = r0 + 16 * m + (lane & 15);
-    if (row >= M) continue;
-#pragma unroll
-    for (int n = 0; n < NB; ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int c = n0 + 16 * n + 4 * (lane >> 4) + r;
-        if (c < N) store_out<OutT>(Y + row * ldy + c, acc[m][n][r]);
-      }
+  for (int q = tid; q < MF * NB * 256; q += 64 * KS) {
+    const int f = q >> 8, e = q & 255, m = f / NB, n = f - m * NB;
+    const int r = e >> 4, c = e & 15;                      // row and column of the fragment
+    const int at = 64 * (c >> 2) + 4 * r + (c & 3);        // its place in the accumulator layout
+    float v = part[0][f][at];
+    for (int w = 1; w < KS; ++w) v += part[w][f][at];
+    const int64_t row = r0 + 16 * m + r;
+    const int col = n0 + 16 * n + c;
+    if (row < p.M && col < p.N) {
+      if (ydt == 2) reinterpret_cast<float*>(Y)[row * ldy + col] = v;
+      else if (ydt == 1) reinterpret_cast<_Float16*>(Y)[row * ldy + col] = (_Float16)v;
+      else reinterpret_cast<uint16_t*>(Y)[row * ldy + col] = f32_to_bf16_rne(v);
+    }
   }
 }
 
-template <int MF, int NB, int KS, int PAT, typename OutT>
-static hipError_t go_skinny(const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
-                            const uint8_t* dns, int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K,
-                            void* Y, int64_t ldy, hipStream_t st) {
-  const int ncg = (N + 16 * NB - 1) / (16 * NB);
-  const int nrt = (int)((M + 16 * MF - 1) / (16 * MF));
-  k_linear_mx_skinny<MF, NB, KS, PAT, OutT><<<dim3((unsigned)(ncg * nrt)), dim3(64 * KS), 0, st>>>(
-      spc, spm, sps, dnc, dns, M, wc, ws, N, K, reinterpret_cast<OutT*>(Y), ldy, ncg, nrt);
+template <int MF, int NB, int KS, int PAT>
+static hipError_t go_skinny(const SkinnyArgs& p, void* Y, int ydt, int64_t ldy, hipStream_t st) {
+  const int ncg = (p.N + 16 * NB - 1) / (16 * NB);
+  const int nrt = (int)((p.M + 16 * MF - 1) / (16 * MF));
+  const dim3 grid((unsigned)(ncg * nrt)), block(64 * KS);
+  if constexpr (PAT != 0) {
+    if (p.K % kBK != 0) {
+      k_linear_mx_skinny<MF, NB, KS, PAT, true><<<grid, block, 0, st>>>(p, Y, ydt, ldy, ncg, nrt);
+      return hipGetLastError();
+    }
+  }
+  k_linear_mx_skinny<MF, NB, KS, PAT, false><<<grid, block, 0, st>>>(p, Y, ydt, ldy, ncg, nrt);
   return hipGetLastError();
 }
 
@@ -1382,19 +1422,39 @@ static hipError_t go_skinny(const uint8_t* spc, const uint8_t* spm, const uint8_
 // fragments per wavefront, for M > 16 wavefronts alone) to keep HBM busy,
 // at least 4 panels per wavefront, at most `cap` wavefronts per workgroup.
 static int skinny_split(int wgs, int K, int cap) {
-  const int nks = K / kBK;
+  const int nks = (K + kBK - 1) / kBK;
   int ks = 4;
   while (ks < cap && wgs * ks * 2 <= 8192 && nks >= 4 * ks * 2) ks *= 2;
   return ks;
 }
 
+// Above 32 rows the workgroups tile M as well.  Each configuration's time is
+// that of one workgroup (us at K = 4096, measured with one per CU) times the
+// rounds of workgroups over the CUs; the cheapest runs.
+struct SkinnyWide {
+  int mf, nb, ks;
+  double us_4096;
+};
+
+static SkinnyWide skinny_wide(int64_t M, int N) {
+  constexpr SkinnyWide cfgs[5] = {{1, 1, 8, 1.8}, {2, 1, 8, 3.2}, {2, 2, 8, 4.2}, {2, 4, 8, 6.2}, {4, 4, 4, 11.5}};
+  const int cus = device_cus();
+  SkinnyWide best{};
+  for (const SkinnyWide& c : cfgs) {
+    const int64_t wgs = (int64_t)((N + 16 * c.nb - 1) / (16 * c.nb)) * ((M + 16 * c.mf - 1) / (16 * c.mf));
+    const double us = c.us_4096 * (double)((wgs + cus - 1) / cus);
+    if (best.mf == 0 || us < best.us_4096) best = {c.mf, c.nb, c.ks, us};
+  }
+  return best;
+}
+
 // (row fragments, column fragments, K splits) by M: every activation block
 // expansion feeds NB column fragments; the K split keeps enough wavefronts
 // streaming the weight.  Above 16 rows the workgroups tile M by 32 or 64.
-template <int PAT, typename OutT>
-static hipError_t go_skinny_m(const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
-                              const uint8_t* dns, int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K,
-                              void* Y, int64_t ldy, hipStream_t st) {
+template <int PAT>
+static hipError_t go_skinny_m(const SkinnyArgs& p, void* Y, int ydt, int64_t ldy, hipStream_t st) {
+  const int64_t M = p.M;
+  const int N = p.N, K = p.K;
   if (M <= 16) {
     // Column fragments: as many as leave at least 192 workgroups (one
     // workgroup runs on one CU), since each activation block loaded and
@@ -1406,7 +1466,7 @@ static hipError_t go_skinny_m(const uint8_t* spc, const uint8_t* spm, const uint
     const int nb = (N + 63) / 64 >= 192 ? 4 : (N + 31) / 32 >= 192 ? 2 : 1;
     const int ks = skinny_split((N + 15) / 16, K, nb == 4 ? 8 : 16);
 #define SHARQ_SKINNY1(NB_, KS_) \
-  if (nb == NB_ && ks == KS_) return go_skinny<1, NB_, KS_, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
+  if (nb == NB_ && ks == KS_) return go_skinny<1, NB_, KS_, PAT>(p, Y, ydt, ldy, st);
     SHARQ_SKINNY1(4, 4) SHARQ_SKINNY1(4, 8)
     SHARQ_SKINNY1(2, 4) SHARQ_SKINNY1(2, 8) SHARQ_SKINNY1(2, 16)
     SHARQ_SKINNY1(1, 4) SHARQ_SKINNY1(1, 8) SHARQ_SKINNY1(1, 16)
@@ -1418,58 +1478,36 @@ static hipError_t go_skinny_m(const uint8_t* spc, const uint8_t* spm, const uint
     // columns (M = 32 gate_up from HBM: 32.1 -> 26.0 µs), else 2.
     const int ks = skinny_split((N + 15) / 16, K, 8);
     if ((N + 63) / 64 >= 192)
-      return ks == 8 ? go_skinny<2, 4, 8, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st)
-                     : go_skinny<2, 4, 4, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-    return ks == 8 ? go_skinny<2, 2, 8, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st)
-                   : go_skinny<2, 2, 4, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
+      return ks == 8 ? go_skinny<2, 4, 8, PAT>(p, Y, ydt, ldy, st)
+                     : go_skinny<2, 4, 4, PAT>(p, Y, ydt, ldy, st);
+    return ks == 8 ? go_skinny<2, 2, 8, PAT>(p, Y, ydt, ldy, st)
+                   : go_skinny<2, 2, 4, PAT>(p, Y, ydt, ldy, st);
   }
-  // Above 32 rows the workgroups tile M by 32 or 64.  Of the configurations
-  // (row fragments, column fragments, K splits) below, those that leave at
-  // least 192 workgroups (one workgroup runs on one CU; fewer leave CUs
-  // idle), and of them the one whose wavefront count is nearest to 1024 in
-  // ratio (ties to the first).  Measured on the Llama decode shapes with the
-  // weight streamed from HBM (µs): M = 64 qkv 12.5 -> 11.8; M = 128 qkv
-  // 23.6 -> 19.4, down 30.1 -> 28.5.
-  struct Cfg { int mf, nb, ks; };
-  constexpr Cfg cfgs[4] = {{4, 4, 4}, {2, 4, 4}, {2, 2, 4}, {2, 2, 8}};
-  const auto wgs = [&](const Cfg& c) {
-    return (int64_t)((N + 16 * c.nb - 1) / (16 * c.nb)) * ((M + 16 * c.mf - 1) / (16 * c.mf));
-  };
-  const auto dist = [](int64_t w) { return w >= 1024 ? (double)w / 1024.0 : 1024.0 / (double)w; };
-  int best = -1;
-  for (int pass = 0; pass < 2 && best < 0; ++pass)   // pass 1 only when no configuration has 192 workgroups
-    for (int i = 0; i < 4; ++i)
-      if ((pass == 1 || wgs(cfgs[i]) >= 192) &&
-          (best < 0 || dist(wgs(cfgs[i]) * cfgs[i].ks) < dist(wgs(cfgs[best]) * cfgs[best].ks)))
-        best = i;
-  switch (best) {
-    case 0: return go_skinny<4, 4, 4, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-    case 1: return go_skinny<2, 4, 4, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-    case 2: return go_skinny<2, 2, 4, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-    default: return go_skinny<2, 2, 8, PAT, OutT>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-  }
+  const SkinnyWide w = skinny_wide(M, N);
+#define SHARQ_SKINNY(MF_, NB_, KS_) \
+  if (w.mf == MF_ && w.nb == NB_ && w.ks == KS_) return go_skinny<MF_, NB_, KS_, PAT>(p, Y, ydt, ldy, st);
+  SHARQ_SKINNY(1, 1, 8) SHARQ_SKINNY(2, 1, 8) SHARQ_SKINNY(2, 2, 8) SHARQ_SKINNY(2, 4, 8) SHARQ_SKINNY(4, 4, 4)
+#undef SHARQ_SKINNY
+  return hipErrorInvalidValue;   // unreachable
 }
 
-// The small-M kernel serves M <= 32, and M <= 256 while the main kernel
-// would have fewer than 48 tiles of 128 x 256 (measured on the Llama decode
-// shapes: at 48 tiles the two are even; at 112 the main kernel is faster,
-// 32.5 against 41.1 µs for gate_up at M = 64 with the weight streamed from
-// HBM, and twice as fast at M = 128).
+// The small-M kernel serves M <= 32, and larger M where its estimate is 15%
+// below the main kernel's (3 us and, per round of 128 x 256 tiles over the CUs,
+// 0.6 us a panel, up to 1.5 times that with every CU running).  Measured,
+// small-M / main kernel, us: N 1024 K 4096 M 256 6.7 / 23, M 1024 15 / 23; N 6144 K
+// 4096 M 96 14 / 23, M 160 16 / 23, M 256 24 / 23, M 512 39 / 24; N 4096 K 14336 M
+// 256 35 / 68, M 512 67 / 70; N 28672 K 4096 M 48 30 / 24; N 2048 K 2048 M 512 9.9 /
+// 14, M 768 15 / 14.
 static bool use_skinny(int64_t M, int N, int K) {
-  if (K % kBK != 0) return false;
+  if (K < kBK) return false;
   if (M <= kSkinnyMaxM) return true;
-  const int64_t tiles = ((M + kBM - 1) / kBM) * (int64_t)((N + 255) / 256);
-  return M <= kSkinnyMaxRowTiled && tiles < 48;
+  if (M > 4096) return false;
+  const int64_t tiles = ((M + kBM - 1) / kBM) * (int64_t)((N + 255) / 256), cus = device_cus();
+  const double rounds = (double)((tiles + cus - 1) / cus), fill = tiles < cus ? (double)tiles / (double)cus : 1.0;
+  const double main_us = 3.0 + 0.6 * K / 128.0 * rounds * (1.0 + 0.5 * fill);
+  return 1.15 * (2.5 + skinny_wide(M, N).us_4096 * K / 4096.0) < main_us;
 }
 
-template <int PAT>
-static hipError_t go_skinny_dt(int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps,
-                               const uint8_t* dnc, const uint8_t* dns, int64_t M, const uint8_t* wc,
-                               const uint8_t* ws, int N, int K, void* Y, int64_t ldy, hipStream_t st) {
-  if (ydt == 2) return go_skinny_m<PAT, float>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-  if (ydt == 1) return go_skinny_m<PAT, _Float16>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-  return go_skinny_m<PAT, uint16_t>(spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-}
 
 // ---------------------------------------------------------------------------
 // Path combinations (Sec. 4.4, table "ablation-combination"): the sum of up
@@ -1938,8 +1976,10 @@ static hipError_t go_linear(const uint8_t* spc, const uint8_t* spm, const uint8_
   const int gx = (N + 32 * NF - 1) / (32 * NF), gy = (int)((M + kBM - 1) / kBM);
   if constexpr (SDW && NF == 8) {
     const PersistPlan pl = persist_plan(gx, gy);
-    k_linear_mx_persist<PAT, OutT><<<dim3((unsigned)pl.grid), dim3(256), 0, st>>>(
-        spc, spm, sps, dnc, dns, M, wc, ws, N, K, reinterpret_cast<OutT*>(Y), ldy, gx, gy, pl.full, pl.halves);
+    const auto kernel = K % kBK == 0 ? k_linear_mx_persist<PAT, OutT, false>
+                                     : k_linear_mx_persist<PAT, OutT, PAT != 0>;
+    kernel<<<dim3((unsigned)pl.grid), dim3(256), 0, st>>>(spc, spm, sps, dnc, dns, M, wc, ws, N, K,
+                                                          reinterpret_cast<OutT*>(Y), ldy, gx, gy, pl.full, pl.halves);
   } else {
     k_linear_mx<NF, PAT, SDW, OutT><<<dim3((unsigned)(gx * gy)), dim3(256), 0, st>>>(
         spc, spm, sps, dnc, dns, M, wc, ws, N, K, reinterpret_cast<OutT*>(Y), ldy, gx, gy);
@@ -1963,7 +2003,7 @@ static hipError_t go_dense_backbone(const uint8_t* spd, const uint8_t* sps, cons
                                     int64_t ldy, hipStream_t st) {
   const int gx = (N + 255) / 256, gy = (int)((M + kBM - 1) / kBM);
   const PersistPlan pl = persist_plan(gx, gy);
-  k_linear_mx_persist<0, OutT><<<dim3((unsigned)pl.grid), dim3(256), 0, st>>>(
+  k_linear_mx_persist<0, OutT, false><<<dim3((unsigned)pl.grid), dim3(256), 0, st>>>(
       spd, nullptr, sps, dnc, dns, M, wc, ws, N, K, reinterpret_cast<OutT*>(Y), ldy, gx, gy, pl.full, pl.halves);
   return hipGetLastError();
 }
@@ -1974,18 +2014,18 @@ static hipError_t go_dense_backbone(const uint8_t* spd, const uint8_t* sps, cons
 hipError_t launch_linear_mx(int pat, int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps,
                             const uint8_t* dnc, const uint8_t* dns, int64_t M, const uint8_t* wc, const uint8_t* ws,
                             int N, int K, void* Y, int64_t ldy, const uint8_t* spd, hipStream_t st) {
-  const bool sdw = (K % kBK) == 0;
+  const bool sdw = K >= kBK;   // at least one full panel
   constexpr int NF = 8;
-  if (spd && sdw && !use_skinny(M, N, K)) {
+  if (spd && K % kBK == 0 && !use_skinny(M, N, K)) {
     if (ydt == 2) return go_dense_backbone<float>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     if (ydt == 1) return go_dense_backbone<_Float16>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     return go_dense_backbone<uint16_t>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
   }
   if (use_skinny(M, N, K)) {
     if (spc == nullptr)   // the backbone exists as its dense copy only
-      return go_skinny_dt<0>(ydt, spd, nullptr, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
-    return pat == 24 ? go_skinny_dt<24>(ydt, spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st)
-                     : go_skinny_dt<48>(ydt, spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
+      return go_skinny_m<0>(SkinnyArgs{spd, nullptr, sps, dnc, dns, wc, ws, M, N, K}, Y, ydt, ldy, st);
+    const SkinnyArgs p{spc, spm, sps, dnc, dns, wc, ws, M, N, K};
+    return pat == 24 ? go_skinny_m<24>(p, Y, ydt, ldy, st) : go_skinny_m<48>(p, Y, ydt, ldy, st);
   }
   if (spc == nullptr) return hipErrorInvalidValue;   // rejected by the C ABI (K not a multiple of 128)
   if (pat == 24) {
@@ -2008,12 +2048,14 @@ static hipError_t go_grouped(const uint8_t* spc, const uint8_t* spm, const uint8
   if constexpr (SDW && NF == 8) {
     const int64_t bound = (int64_t)gx * items, cus = device_cus();
     const unsigned g = (unsigned)(bound < cus ? bound : cus);
-    if (ridx)
-      k_linear_mx_grouped_persist<PAT, OutT, true><<<dim3(g), dim3(256), 0, st>>>(
-          spc, spm, sps, dnc, dns, ridx, act_rows, offs, E, wc, ws, N, K, reinterpret_cast<OutT*>(Y), ldy, gx);
-    else
-      k_linear_mx_grouped_persist<PAT, OutT, false><<<dim3(g), dim3(256), 0, st>>>(
-          spc, spm, sps, dnc, dns, ridx, act_rows, offs, E, wc, ws, N, K, reinterpret_cast<OutT*>(Y), ldy, gx);
+    constexpr bool kTail = PAT != 0;   // the dense backbone copy needs K a multiple of 128
+    const bool tail = K % kBK != 0;
+    const auto kernel = ridx ? (tail ? k_linear_mx_grouped_persist<PAT, OutT, kTail, true>
+                                     : k_linear_mx_grouped_persist<PAT, OutT, false, true>)
+                             : (tail ? k_linear_mx_grouped_persist<PAT, OutT, kTail, false>
+                                     : k_linear_mx_grouped_persist<PAT, OutT, false, false>);
+    kernel<<<dim3(g), dim3(256), 0, st>>>(spc, spm, sps, dnc, dns, ridx, act_rows, offs, E, wc, ws, N, K,
+                                          reinterpret_cast<OutT*>(Y), ldy, gx);
     return hipGetLastError();
   }
   dim3 grid((unsigned)(gx * items)), block(256);
@@ -2042,9 +2084,12 @@ hipError_t launch_linear_mx_grouped(int pat, int ydt, const uint8_t* spc, const 
                                     const uint8_t* dnc, const uint8_t* dns, const int32_t* ridx, int64_t act_rows,
                                     const int32_t* offs, int E, int64_t total, const uint8_t* wc, const uint8_t* ws,
                                     int N, int K, void* Y, int64_t ldy, const uint8_t* spd, hipStream_t st) {
-  const bool sdw = (K % kBK) == 0;
+  // at least one full panel, and every expert's scales at a multiple of 4
+  // bytes (K not a multiple of 128 can leave them anywhere), as the
+  // interleaved pipeline's loads need
+  const bool sdw = K >= kBK && ((int64_t)N * (K / 32)) % 4 == 0;
   constexpr int NF = 8;
-  if (spd && sdw)
+  if (spd && K % kBK == 0)
     return go_grouped_dt<NF, 0, true>(ydt, spd, nullptr, sps, dnc, dns, ridx, act_rows, offs, E, total, wc, ws, N, K,
                                       Y, ldy, st);
   if (pat == 24) {
