@@ -28,6 +28,8 @@
 
 #include "sharq_prep_block.hpp"
 
+#include <algorithm>
+
 #pragma clang fp contract(off)
 
 namespace sharq {
@@ -146,38 +148,91 @@ __global__ __launch_bounds__(256) void k_prep_blocks(XSrc src, int M, int K, Act
 
 // ---------------------------------------------------------------------------
 // NVFP4 per-tensor scale (App. A.1.3): S = amax(y) / 2688 over the whole call,
-// 1 for an all-zero tensor.  The running maximum is kept as the bit pattern
-// of a non-negative float in the output's tensor_scale slot (bit patterns of
-// non-negative floats order like the floats), then replaced by S.
+// 1 for an all-zero tensor.  A pre-pass leaves one partial maximum per
+// workgroup in an output code buffer (which the preparation overwrites
+// afterwards), and one workgroup reduces them to S: two launches, where a
+// running maximum in the tensor_scale slot took three (clear, atomics of ~12
+// ns each that serialize on the slot, divide).
 // ---------------------------------------------------------------------------
-
-__global__ void k_store_u32(uint32_t* p, uint32_t v) { *p = v; }
 
 __global__ void k_copy_f32(const float* src, float* dst) { *dst = *src; }
 
-__global__ void k_pts_finalize(uint32_t* slot) {
-  const float amax = __uint_as_float(*slot);
-  const float S = amax > 0.0f ? amax / 2688.0f : 1.0f;
-  *reinterpret_cast<float*>(slot) = S;
+constexpr int kAmaxWG = 1024;   // most workgroups, and partial maxima, of the pre-pass
+
+__global__ __launch_bounds__(256) void k_pts_finalize(const float* part, int n, float* ts) {
+  __shared__ float wmax[4];
+  float m = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kAmaxWG / 256; ++i) {
+    const int j = (int)threadIdx.x + 256 * i;
+    if (j < n) m = fmaxf(m, part[j]);
+  }
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const float amax = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    *ts = amax > 0.0f ? amax / 2688.0f : 1.0f;
+  }
 }
 
-// The pre-pass walks row groups grid-stride (one row per wavefront at a
-// time) and issues one atomicMax per workgroup: atomics on one address
-// serialize (~12 ns each measured), so one per row cost ~25 us at M = 2048.
-// The grid is capped at kAmaxWG workgroups.
-constexpr int kAmaxWG = 256;
-
-__device__ __forceinline__ void amax_publish(float m, uint32_t* slot, float* wmax) {
+__device__ __forceinline__ void amax_publish(float m, float* part, float* wmax) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   m = wave_max(m);
   if (lane == 0) wmax[wave] = m;
   __syncthreads();
-  if (threadIdx.x == 0) atomicMax(slot, __float_as_uint(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]))));
+  if (threadIdx.x == 0) part[blockIdx.x] = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
 }
 
+// With RMSNorm, rows of up to 256 blocks: the structure of k_prep_norm_split,
+// C wavefronts per row, the workgroup walking groups of 4 / C rows (M = 2048, K =
+// 4096: 5.6 us, 8.0 with one wavefront per row; M = 4096, K = 3584: 9.8, 13.9).
+template <int C, bool RES>
+__global__ __launch_bounds__(256) void k_amax_norm_split(XSrc src, int M, int K, const uint16_t* __restrict__ gamma,
+                                                         float eps, float* out) {
+  __shared__ float part[2][4];
+  __shared__ float wmax[4];
+  constexpr int RPG = 4 / C;   // rows per group
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int nblk = K / 32, b = (wave % C) * 64 + lane;
+  const bool live = b < nblk;
+  const int bl = live ? b : nblk - 1;   // lanes past the row reread its last block and add 0 to the sum
+  uint4 gq[4];
+  const uint4* gr = reinterpret_cast<const uint4*>(gamma);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) gq[j] = gr[4 * bl + j];
+  float m = 0.0f;
+  int it = 0;
+  for (int64_t g = blockIdx.x; g * RPG < M; g += gridDim.x, ++it) {
+    int64_t row = g * RPG + wave / C;
+    if (row >= M) row = M - 1;   // a repeated row does not change the maximum
+    uint4 xq[4];
+    load_block<RES>(src, row, bl, xq, false);
+    float x[32];
+    unpack_bf16x32(xq, x);
+    const float bs = block_sum_sq(x);
+    const float cs = wave_tree_sum(live ? bs : 0.0f);
+    float total = cs;
+    if (C > 1) {
+      float* p = part[it & 1];   // alternating: one barrier per group
+      if (lane == 0) p[wave] = cs;
+      __syncthreads();
+      const int base = (wave / C) * C;
+      if (C == 2) total = p[base] + p[base + 1];
+      else total = (p[base] + p[base + 1]) + (p[base + 2] + p[base + 3]);
+    }
+    const float r = (float)(1.0 / __builtin_sqrt((double)total / (double)K + (double)eps));
+    float y[32];
+    norm_block(xq, gq, r, y);
+    m = fmaxf(m, absmax32(y));
+  }
+  amax_publish(m, out, wmax);
+}
+
+// Longer rows: one row per wavefront, NB blocks per lane.
 template <int NB, bool RES>
 __global__ __launch_bounds__(256) void k_amax_norm(XSrc src, int M, int K, const uint16_t* __restrict__ gamma,
-                                                   float eps, uint32_t* slot) {
+                                                   float eps, float* out) {
   __shared__ float wmax[4];
   const int lane = threadIdx.x & 63;
   const int nblk = K / 32;
@@ -198,24 +253,31 @@ __global__ __launch_bounds__(256) void k_amax_norm(XSrc src, int M, int K, const
       m = fmaxf(m, absmax32(y));
     }
   }
-  amax_publish(m, slot, wmax);   // every wavefront reaches the barrier inside
+  amax_publish(m, out, wmax);   // every wavefront reaches the barrier inside
 }
 
+// Without RMSNorm: eight elements (one 16-byte load of each input) per thread
+// and step, so that few rows still spread over the chip (SiLU.mul at M = 4, K =
+// 14336: 3.3 us, 27 with one wavefront per row).
 template <int SRC>
-__global__ __launch_bounds__(256) void k_amax_plain(XSrc src, int M, int K, uint32_t* slot) {
+__global__ __launch_bounds__(256) void k_amax_plain(XSrc src, int M, int K, float* out) {
   __shared__ float wmax[4];
-  const int lane = threadIdx.x & 63;
+  const uint32_t per = (uint32_t)K / 8u;
   float m = 0.0f;
-  for (int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < M; row += (int64_t)gridDim.x * 4) {
-    for (int b = lane; b < K / 32; b += 64) {
-      uint4 q[4];
-      load_block<SRC>(src, row, b, q, false);
-      float y[32];
-      unpack_bf16x32(q, y);
-      m = fmaxf(m, absmax32(y));
+  for (int64_t row = blockIdx.y; row < M; row += gridDim.y) {
+    for (uint32_t c = blockIdx.x * 256u + threadIdx.x; c < per; c += gridDim.x * 256u) {
+      const uint4 q = load_chunk<SRC>(src, row, c);
+      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) m = fmaxf(m, fmaxf(fabsf(bf16_lo(w[j])), fabsf(bf16_hi(w[j]))));
     }
   }
-  amax_publish(m, slot, wmax);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  m = wave_max(m);
+  if (lane == 0) wmax[wave] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    out[blockIdx.y * gridDim.x + blockIdx.x] = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
 }
 
 // ---------------------------------------------------------------------------
@@ -554,19 +616,30 @@ static void go_prep(const XSrc& src, int M, int K, const uint16_t* gamma, float 
     k_prep_norm<8, PAT, NV, RES><<<grid, block, 0, st>>>(src, M, K, gamma, eps, o, S_ptr);
 }
 
-template <bool RES>
-static void go_amax(const XSrc& src, int M, int K, const uint16_t* gamma, float eps, uint32_t* slot, dim3 rows_grid,
+// The per-tensor scale of y into ts.  part: scratch for the partial maxima, a
+// code buffer of the activation (K / 4 or K / 2 bytes per row, so at least 4
+// bytes per row, and per workgroup here).  SRC as in load_block.
+template <int SRC>
+static void go_amax(const XSrc& src, int M, int K, const uint16_t* gamma, float eps, uint8_t* scratch, float* ts,
                     hipStream_t st) {
-  const dim3 grid(rows_grid.x < (unsigned)kAmaxWG ? rows_grid.x : (unsigned)kAmaxWG);
+  float* part = reinterpret_cast<float*>(scratch);
+  unsigned n;
   if (gamma == nullptr) {
-    k_amax_plain<RES ? 1 : 0><<<grid, 256, 0, st>>>(src, M, K, slot);
-    return;
+    // x: a row's chunks of 2048 positions; y: rows, up to 1024 workgroups in all
+    const unsigned gx = (unsigned)std::min((K + 2047) / 2048, 64);
+    const unsigned gy = (unsigned)std::min<int64_t>(M, kAmaxWG / gx);
+    n = gx * gy;
+    k_amax_plain<SRC><<<dim3(gx, gy), 256, 0, st>>>(src, M, K, part);
+  } else if constexpr (SRC != 2) {
+    const int nblk = K / 32;
+    const int rpg = nblk <= 64 ? 4 : nblk <= 128 ? 2 : nblk <= 256 ? 1 : 4;
+    n = (unsigned)std::min<int64_t>(((int64_t)M + rpg - 1) / rpg, kAmaxWG);
+    if (nblk <= 64) k_amax_norm_split<1, SRC == 1><<<n, 256, 0, st>>>(src, M, K, gamma, eps, part);
+    else if (nblk <= 128) k_amax_norm_split<2, SRC == 1><<<n, 256, 0, st>>>(src, M, K, gamma, eps, part);
+    else if (nblk <= 256) k_amax_norm_split<4, SRC == 1><<<n, 256, 0, st>>>(src, M, K, gamma, eps, part);
+    else k_amax_norm<8, SRC == 1><<<n, 256, 0, st>>>(src, M, K, gamma, eps, part);
   }
-  const int chunks = (K / 32 + 63) / 64;
-  if (chunks <= 1) k_amax_norm<1, RES><<<grid, 256, 0, st>>>(src, M, K, gamma, eps, slot);
-  else if (chunks <= 2) k_amax_norm<2, RES><<<grid, 256, 0, st>>>(src, M, K, gamma, eps, slot);
-  else if (chunks <= 4) k_amax_norm<4, RES><<<grid, 256, 0, st>>>(src, M, K, gamma, eps, slot);
-  else k_amax_norm<8, RES><<<grid, 256, 0, st>>>(src, M, K, gamma, eps, slot);
+  k_pts_finalize<<<1, 256, 0, st>>>(part, (int)n, ts);
 }
 
 template <bool RES>
@@ -597,11 +670,8 @@ hipError_t launch_prep(const uint16_t* X, int M, int K, int64_t ldx, const uint1
     if (ts_in) {
       k_copy_f32<<<1, 1, 0, st>>>(ts_in, ts_out);
     } else {
-      uint32_t* slot = reinterpret_cast<uint32_t*>(ts_out);
-      k_store_u32<<<1, 1, 0, st>>>(slot, 0u);
-      if (res) go_amax<true>(src, M, K, gamma, eps, slot, grid, st);
-      else go_amax<false>(src, M, K, gamma, eps, slot, grid, st);
-      k_pts_finalize<<<1, 1, 0, st>>>(slot);
+      if (res) go_amax<1>(src, M, K, gamma, eps, dnc, ts_out, st);
+      else go_amax<0>(src, M, K, gamma, eps, dnc, ts_out, st);
     }
   }
   if (res) go_prep_pat<true>(pat, nv, src, M, K, gamma, eps, o, ts_out, grid, st);
@@ -643,10 +713,7 @@ hipError_t launch_prep_mode(int mode, const uint16_t* X, int M, int K, int64_t l
     if (ts_in) {
       k_copy_f32<<<1, 1, 0, st>>>(ts_in, ts_out);
     } else {
-      uint32_t* slot = reinterpret_cast<uint32_t*>(ts_out);
-      k_store_u32<<<1, 1, 0, st>>>(slot, 0u);
-      go_amax<false>(src, M, K, gamma, eps, slot, grid, st);
-      k_pts_finalize<<<1, 1, 0, st>>>(slot);
+      go_amax<0>(src, M, K, gamma, eps, path1_kind(mode) != kPathNone ? c1 : c2, ts_out, st);
     }
   }
   const float* S = nv ? ts_out : nullptr;
@@ -693,10 +760,7 @@ hipError_t launch_prep_silu(const uint16_t* gate, const uint16_t* up, uint16_t* 
     if (ts_in) {
       k_copy_f32<<<1, 1, 0, st>>>(ts_in, ts_out);
     } else {
-      uint32_t* slot = reinterpret_cast<uint32_t*>(ts_out);
-      k_store_u32<<<1, 1, 0, st>>>(slot, 0u);
-      k_amax_plain<2><<<grid, 256, 0, st>>>(src, M, K, slot);
-      k_pts_finalize<<<1, 1, 0, st>>>(slot);
+      go_amax<2>(src, M, K, nullptr, 0.0f, dnc, ts_out, st);
     }
   }
   const int nblk = K / 32;

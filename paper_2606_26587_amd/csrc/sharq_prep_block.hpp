@@ -704,6 +704,18 @@ __device__ __forceinline__ void load_block(const XSrc& s, int64_t row, int b, ui
   }
 }
 
+// Eight values (16-byte piece c of `row`) of the same sources; h is not stored.
+template <int SRC>
+__device__ __forceinline__ uint4 load_chunk(const XSrc& s, int64_t row, uint32_t c) {
+  const uint4 q = reinterpret_cast<const uint4*>(s.X + row * s.ldx)[c];
+  if (SRC == 0) return q;
+  const uint4 r = reinterpret_cast<const uint4*>(s.Rs + row * s.ldr)[c];
+  if (SRC == 1)
+    return make_uint4(add_bf16x2(q.x, r.x), add_bf16x2(q.y, r.y), add_bf16x2(q.z, r.z), add_bf16x2(q.w, r.w));
+  return make_uint4(silu_mul_bf16x2(q.x, r.x), silu_mul_bf16x2(q.y, r.y), silu_mul_bf16x2(q.z, r.z),
+                    silu_mul_bf16x2(q.w, r.w));
+}
+
 // Load a row's blocks (NB per lane) and return its RMSNorm reciprocal r.
 template <int NB, bool RES>
 __device__ __forceinline__ float load_row_rms(const XSrc& src, int64_t row, bool write_h, int lane, int nblk, int K,
