@@ -2008,6 +2008,12 @@ static hipError_t go_dense_backbone(const uint8_t* spd, const uint8_t* sps, cons
   return hipGetLastError();
 }
 
+// The 8-wavefront kernel on a dense backbone copy (sharq_mx8.hip).
+bool use_mx8(int64_t M, int N);
+hipError_t launch_linear_mx8(int ydt, const uint8_t* spd, const uint8_t* sps, const uint8_t* dnc, const uint8_t* dns,
+                             int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K, void* Y, int64_t ldy,
+                             hipStream_t st);
+
 // spd (optional): the backbone's dense copy; used by the main kernel (K a
 // multiple of 128, M beyond the small-M kernel's range), which then skips the
 // expansion.
@@ -2017,6 +2023,7 @@ hipError_t launch_linear_mx(int pat, int ydt, const uint8_t* spc, const uint8_t*
   const bool sdw = K >= kBK;   // at least one full panel
   constexpr int NF = 8;
   if (spd && K % kBK == 0 && !use_skinny(M, N, K)) {
+    if (use_mx8(M, N)) return launch_linear_mx8(ydt, spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     if (ydt == 2) return go_dense_backbone<float>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     if (ydt == 1) return go_dense_backbone<_Float16>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     return go_dense_backbone<uint16_t>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
