@@ -1280,8 +1280,8 @@ struct SkinnyArgs {
 // narrower last panel, lanes whose block lies past K reread block 0 (and zero
 // its weight codes in skinny_step).
 template <int MF, int NB, int PAT, bool RAG>
-__device__ __forceinline__ void skinny_load(SkinnyStage<MF, NB>& st, const SkinnyArgs& p, int64_t r0, int n0, int ks,
-                                            int lane) {
+__device__ __forceinline__ void skinny_load(SkinnyStage<MF, NB>& st, const SkinnyArgs& p, const int64_t (&row)[MF],
+                                            int n0, int ks, int lane) {
   const int nb = RAG ? min(128, p.K - 128 * ks) >> 5 : 4;   // blocks of this panel
   const int j = RAG && (lane >> 4) >= nb ? 0 : lane >> 4;   // block within the panel
   const int64_t pn = (int64_t)ks * p.N * 4, pm = (int64_t)ks * p.M * 4;   // blocks before it
@@ -1293,9 +1293,7 @@ __device__ __forceinline__ void skinny_load(SkinnyStage<MF, NB>& st, const Skinn
   }
 #pragma unroll
   for (int m = 0; m < MF; ++m) {
-    int64_t row = r0 + 16 * m + (lane & 15);
-    if (row >= p.M) row = p.M - 1;
-    const int64_t V = pm + row * nb + j;   // block-major index of (row, block)
+    const int64_t V = pm + row[m] * nb + j;   // block-major index of (row, block)
     st.dn[m] = *reinterpret_cast<const uint4*>(p.dnc + V * 16);
     if (PAT == 0) {
       st.spd[m] = *reinterpret_cast<const uint4*>(p.spc + V * 16);
@@ -1350,15 +1348,13 @@ __device__ __forceinline__ void skinny_tile(int id, int ncg, int nrt, int& cg, i
   rt = idp - cg * nrt;
 }
 
+// One tile of 16 MF rows (the lane's are `row`) x 16 NB columns by the KS
+// wavefronts of a workgroup, into Y rows [y0, y_end).
 template <int MF, int NB, int KS, int PAT, bool RAG>
-__global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(SkinnyArgs p, void* Y, int ydt, int64_t ldy, int ncg,
-                                                              int nrt) {
-  __shared__ float part[KS][MF * NB][256];
+__device__ __forceinline__ void skinny_compute(const SkinnyArgs& p, const int64_t (&row)[MF], int64_t y0,
+                                               int64_t y_end, int n0, void* Y, int ydt, int64_t ldy,
+                                               float (&part)[KS][MF * NB][256]) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  int cg, rt;
-  skinny_tile(blockIdx.x, ncg, nrt, cg, rt);
-  const int n0 = cg * 16 * NB;
-  const int64_t r0 = (int64_t)rt * 16 * MF;
   const int nks = (p.K + kBK - 1) / kBK;
   const int per = (nks + KS - 1) / KS;
   const int k0 = wave * per, k1 = min(nks, k0 + per);
@@ -1370,14 +1366,14 @@ __global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(SkinnyArgs p, void
     for (int n = 0; n < NB; ++n) acc[m][n] = v4f_t{0.0f, 0.0f, 0.0f, 0.0f};
 
   SkinnyStage<MF, NB> s0, s1;
-  if (k0 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, r0, n0, k0, lane);
-  if (k0 + 1 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, r0, n0, k0 + 1, lane);
+  if (k0 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, row, n0, k0, lane);
+  if (k0 + 1 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, row, n0, k0 + 1, lane);
   int ks = k0;
   for (; ks + 1 < k1; ks += 2) {
     skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
-    if (ks + 2 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, r0, n0, ks + 2, lane);
+    if (ks + 2 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, row, n0, ks + 2, lane);
     skinny_step<MF, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
-    if (ks + 3 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, r0, n0, ks + 3, lane);
+    if (ks + 3 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, row, n0, ks + 3, lane);
   }
   if (ks < k1) skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
 
@@ -1393,14 +1389,142 @@ __global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(SkinnyArgs p, void
     const int at = 64 * (c >> 2) + 4 * r + (c & 3);        // its place in the accumulator layout
     float v = part[0][f][at];
     for (int w = 1; w < KS; ++w) v += part[w][f][at];
-    const int64_t row = r0 + 16 * m + r;
+    const int64_t yr = y0 + 16 * m + r;
     const int col = n0 + 16 * n + c;
-    if (row < p.M && col < p.N) {
-      if (ydt == 2) reinterpret_cast<float*>(Y)[row * ldy + col] = v;
-      else if (ydt == 1) reinterpret_cast<_Float16*>(Y)[row * ldy + col] = (_Float16)v;
-      else reinterpret_cast<uint16_t*>(Y)[row * ldy + col] = f32_to_bf16_rne(v);
+    if (yr < y_end && col < p.N) {
+      if (ydt == 2) reinterpret_cast<float*>(Y)[yr * ldy + col] = v;
+      else if (ydt == 1) reinterpret_cast<_Float16*>(Y)[yr * ldy + col] = (_Float16)v;
+      else reinterpret_cast<uint16_t*>(Y)[yr * ldy + col] = f32_to_bf16_rne(v);
     }
   }
+}
+
+template <int MF, int NB, int KS, int PAT, bool RAG>
+__global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(SkinnyArgs p, void* Y, int ydt, int64_t ldy, int ncg,
+                                                              int nrt) {
+  __shared__ float part[KS][MF * NB][256];
+  const int lane = threadIdx.x & 63;
+  int cg, rt;
+  skinny_tile(blockIdx.x, ncg, nrt, cg, rt);
+  const int64_t r0 = (int64_t)rt * 16 * MF;
+  int64_t row[MF];
+#pragma unroll
+  for (int m = 0; m < MF; ++m) {
+    row[m] = r0 + 16 * m + (lane & 15);
+    if (row[m] >= p.M) row[m] = p.M - 1;   // loads stay in bounds, stores are masked
+  }
+  skinny_compute<MF, NB, KS, PAT, RAG>(p, row, r0, p.M, cg * 16 * NB, Y, ydt, ldy, part);
+}
+
+// Grouped forms for few rows (MoE decode), where the launch streams the
+// experts' weights: a workgroup takes 16 NB columns and up to CH rows of one
+// expert, with no 128-row tiles and, for an expert's first CH rows, no scan over
+// the experts.  The rows of a popular expert beyond those go to total / CH
+// further slots, the first of the grid, which find theirs by a scan (most end
+// there): walking them in one workgroup took 55 us instead of 7.6 where all 512
+// rows have one expert of 128 (N 2048, K 768).  extra >= the sum over experts
+// of (rows - 1) / CH.
+template <int CH>
+__device__ __forceinline__ bool grouped_chunk(const int32_t* offs, int E, int extra, int slot, int& e, int& lo, int& hi) {
+  int skip = 0;   // chunks of the expert before this one
+  if (slot >= extra) {
+    e = slot - extra;
+  } else {
+    const int lane = threadIdx.x & 63;
+    int base = 0, before = 0;
+    for (;; base += 64) {   // the same in every lane
+      if (base >= E) return false;
+      const int ex = base + lane;
+      const int rows = ex < E ? offs[ex + 1] - offs[ex] : 0;
+      const int more = rows > CH ? (rows - 1) / CH : 0;
+      int sum = more;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(sum, d);
+        if (lane >= d) sum += up;
+      }
+      const uint64_t in = __ballot(slot < before + sum);
+      if (in != 0) {
+        const int l = __builtin_ctzll(in);
+        e = base + l;
+        skip = slot - before - __shfl(sum - more, l) + 1;
+        break;
+      }
+      before += __shfl(sum, 63);
+    }
+    e = __builtin_amdgcn_readfirstlane(e);
+    skip = __builtin_amdgcn_readfirstlane(skip);
+  }
+  lo = offs[e] + skip * CH;
+  hi = offs[e + 1];
+  if (hi - lo > CH) hi = lo + CH;
+  return hi > lo;
+}
+
+// K split over the KS wavefronts, for column groups that do not fill the chip.
+template <int MF, int NB, int KS, int PAT, bool RAG>
+__global__ __launch_bounds__(64 * KS) void k_linear_mx_grouped_skinny(SkinnyArgs p, const int32_t* ridx,
+                                                                      const int32_t* offs, int E, int extra, void* Y,
+                                                                      int ydt, int64_t ldy, int ncg) {
+  __shared__ float part[KS][MF * NB][256];
+  const int lane = threadIdx.x & 63;
+  const int slot = (int)blockIdx.x / ncg, cg = (int)blockIdx.x - slot * ncg;
+  int e, lo, hi;
+  if (!grouped_chunk<16 * MF>(offs, E, extra, slot, e, lo, hi)) return;   // the same in every wavefront
+  p.wc += (int64_t)e * p.N * (p.K / 2);
+  p.ws += (int64_t)e * p.N * (p.K / 32);
+  int64_t row[MF];
+#pragma unroll
+  for (int m = 0; m < MF; ++m) {
+    int i = lo + 16 * m + (lane & 15);
+    if (i >= hi) i = hi - 1;   // loads stay in bounds, stores are masked
+    row[m] = ridx ? (int64_t)ridx[i] : (int64_t)i;
+  }
+  skinny_compute<MF, NB, KS, PAT, RAG>(p, row, lo, hi, cg * 16 * NB, Y, ydt, ldy, part);
+}
+
+// For many column groups: one wavefront each, without splitting K.  Two row
+// tiles per wavefront (MF 2) cost occupancy and measured 33 us against 24 at
+// E 128, N 2048, K 768, 4 rows a mean; 32 columns 27, 128 columns 26.
+template <int NB, int PAT, bool RAG>
+__global__ __launch_bounds__(64) void k_linear_mx_grouped_rows(SkinnyArgs p, const int32_t* ridx, const int32_t* offs,
+                                                               int E, int extra, void* Y, int ydt, int64_t ldy,
+                                                               int ncg) {
+  const int lane = threadIdx.x;
+  const int slot = (int)blockIdx.x / ncg, cg = (int)blockIdx.x - slot * ncg, n0 = cg * 16 * NB;
+  int e, lo, hi;
+  if (!grouped_chunk<16>(offs, E, extra, slot, e, lo, hi)) return;
+  p.wc += (int64_t)e * p.N * (p.K / 2);
+  p.ws += (int64_t)e * p.N * (p.K / 32);
+  const int nks = (p.K + kBK - 1) / kBK;
+  const int i = lo + (lane & 15), ic = i < hi ? i : hi - 1;   // loads stay in bounds, stores are masked
+  const int64_t row[1] = {ridx ? (int64_t)ridx[ic] : (int64_t)ic};
+  v4f_t acc[1][NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) acc[0][n] = v4f_t{0.0f, 0.0f, 0.0f, 0.0f};
+  SkinnyStage<1, NB> s0, s1;
+  skinny_load<1, NB, PAT, RAG>(s0, p, row, n0, 0, lane);
+  if (nks > 1) skinny_load<1, NB, PAT, RAG>(s1, p, row, n0, 1, lane);
+  int ks = 0;
+  for (; ks + 1 < nks; ks += 2) {
+    skinny_step<1, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
+    if (ks + 2 < nks) skinny_load<1, NB, PAT, RAG>(s0, p, row, n0, ks + 2, lane);
+    skinny_step<1, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
+    if (ks + 3 < nks) skinny_load<1, NB, PAT, RAG>(s1, p, row, n0, ks + 3, lane);
+  }
+  if (ks < nks) skinny_step<1, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
+  if (i >= hi) return;
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int col = n0 + 16 * n + 4 * (lane >> 4) + r;
+      if (col >= p.N) continue;
+      const int64_t at = (int64_t)i * ldy + col;
+      if (ydt == 2) reinterpret_cast<float*>(Y)[at] = acc[0][n][r];
+      else if (ydt == 1) reinterpret_cast<_Float16*>(Y)[at] = (_Float16)acc[0][n][r];
+      else reinterpret_cast<uint16_t*>(Y)[at] = f32_to_bf16_rne(acc[0][n][r]);
+    }
 }
 
 template <int MF, int NB, int KS, int PAT>
@@ -2043,6 +2167,62 @@ hipError_t launch_linear_mx(int pat, int ydt, const uint8_t* spc, const uint8_t*
              : go_linear_dt<NF, 48, false>(ydt, spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
 }
 
+template <int MF, int NB, int KS, int PAT>
+static hipError_t go_grouped_skinny(const SkinnyArgs& p, const int32_t* ridx, const int32_t* offs, int E, int64_t total, void* Y,
+                                    int ydt, int64_t ldy, hipStream_t st) {
+  const int ncg = (p.N + 16 * NB - 1) / (16 * NB);
+  const int extra = (int)(total / (16 * MF));
+  const dim3 grid((unsigned)ncg * (unsigned)(E + extra)), block(64 * KS);
+  if constexpr (PAT != 0) {
+    if (p.K % kBK != 0) {
+      k_linear_mx_grouped_skinny<MF, NB, KS, PAT, true><<<grid, block, 0, st>>>(p, ridx, offs, E, extra, Y, ydt, ldy, ncg);
+      return hipGetLastError();
+    }
+  }
+  k_linear_mx_grouped_skinny<MF, NB, KS, PAT, false><<<grid, block, 0, st>>>(p, ridx, offs, E, extra, Y, ydt, ldy, ncg);
+  return hipGetLastError();
+}
+
+template <int NB, int PAT>
+static hipError_t go_grouped_rows(const SkinnyArgs& p, const int32_t* ridx, const int32_t* offs, int E, int64_t total,
+                                  void* Y, int ydt, int64_t ldy, hipStream_t st) {
+  const int ncg = (p.N + 16 * NB - 1) / (16 * NB);
+  const int extra = (int)(total / 16);
+  const dim3 grid((unsigned)ncg * (unsigned)(E + extra)), block(64);
+  if constexpr (PAT != 0) {
+    if (p.K % kBK != 0) {
+      k_linear_mx_grouped_rows<NB, PAT, true><<<grid, block, 0, st>>>(p, ridx, offs, E, extra, Y, ydt, ldy, ncg);
+      return hipGetLastError();
+    }
+  }
+  k_linear_mx_grouped_rows<NB, PAT, false><<<grid, block, 0, st>>>(p, ridx, offs, E, extra, Y, ydt, ldy, ncg);
+  return hipGetLastError();
+}
+
+// Few rows per expert: by the number of 64-column groups over all experts
+// (many fill the chip without splitting K) and the mean rows of an expert (the
+// host does not know the routing).  Measured, these kernels / the persistent
+// one (us, weights streamed, random routing): E 128 N 2048 K 768, mean 4 rows
+// 24 / 41, 16 41 / 43; E 128 N 1536 K 2048, 4 47 / 62, 16 67 / 65; E 32 N 2048 K 2048,
+// 8 19 / 24, 16 21 / 23; E 8 N 2048 K 4096, 8 9.2 / 24.8, 24 12.6 / 24.9, 32 19.6 /
+// 24.9.  At most 512 rows: where few experts have all of them, the persistent
+// kernel's 128-row tiles re-read less (E 128 N 1536 K 2048, 8 experts: 512 rows 12.4
+// / 11.7, 1024 19.5 / 12.2).
+static bool grouped_many(int E, int N) { return (int64_t)E * ((N + 63) / 64) >= 768; }
+
+static bool use_grouped_skinny(int64_t total, int E, int N) {
+  if (((int64_t)E + 32) * ((N + 31) / 32) > (1 << 30)) return false;   // the grid
+  return total <= 512 && total <= (grouped_many(E, N) ? 8 : 24) * (int64_t)E;
+}
+
+template <int PAT>
+static hipError_t go_grouped_skinny_cfg(const SkinnyArgs& p, const int32_t* ridx, const int32_t* offs, int E,
+                                        int64_t total, void* Y, int ydt, int64_t ldy, hipStream_t st) {
+  if (grouped_many(E, p.N)) return go_grouped_rows<4, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
+  if (total > 8 * (int64_t)E) return go_grouped_skinny<2, 4, 4, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
+  return go_grouped_skinny<1, 2, 4, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
+}
+
 template <int NF, int PAT, bool SDW, typename OutT>
 static hipError_t go_grouped(const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
                              const uint8_t* dns, const int32_t* ridx, int64_t act_rows, const int32_t* offs, int E,
@@ -2096,6 +2276,14 @@ hipError_t launch_linear_mx_grouped(int pat, int ydt, const uint8_t* spc, const 
   // interleaved pipeline's loads need
   const bool sdw = K >= kBK && ((int64_t)N * (K / 32)) % 4 == 0;
   constexpr int NF = 8;
+  if (use_grouped_skinny(total, E, N)) {
+    if (spd && K % kBK == 0)
+      return go_grouped_skinny_cfg<0>(SkinnyArgs{spd, nullptr, sps, dnc, dns, wc, ws, act_rows, N, K}, ridx, offs, E,
+                                      total, Y, ydt, ldy, st);
+    const SkinnyArgs p{spc, spm, sps, dnc, dns, wc, ws, act_rows, N, K};
+    return pat == 24 ? go_grouped_skinny_cfg<24>(p, ridx, offs, E, total, Y, ydt, ldy, st)
+                     : go_grouped_skinny_cfg<48>(p, ridx, offs, E, total, Y, ydt, ldy, st);
+  }
   if (spd && K % kBK == 0)
     return go_grouped_dt<NF, 0, true>(ydt, spd, nullptr, sps, dnc, dns, ridx, act_rows, offs, E, total, wc, ws, N, K,
                                       Y, ldy, st);
