@@ -17,10 +17,9 @@
 // preparation wrote (pattern 0), which spares every column tile the
 // expansion.  The shared weight tile (E2M1 payload + E8M0 scales) is staged
 // through LDS once per K step and read by both MFMAs of every fragment.
-// Also here: the small-M kernel for decode, the grouped (MoE) form, the
-// NVFP4 and HiF4 kernels on 16-bit MFMA over exactly dequantized operands
-// (fp16 in the NVFP4 kernel for K a multiple of 128, bf16 elsewhere), and
-// the generic kernels of the ablation path combinations.
+// Also here: the small-M kernel for decode, the grouped (MoE) forms, the HiF4
+// kernel for larger M with K not a multiple of 128, and the generic kernels of
+// the ablation path combinations.
 
 // MFMA 32x32x64 FP4 operand layout (lane l, 64-wide wavefront): lane l holds
 // row (l % 32) and the 32 K values of block (l / 32) of the 64-wide K slice as
@@ -1425,7 +1424,8 @@ __global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(SkinnyArgs p, void
 // rows have one expert of 128 (N 2048, K 768).  extra >= the sum over experts
 // of (rows - 1) / CH.
 template <int CH>
-__device__ __forceinline__ bool grouped_chunk(const int32_t* offs, int E, int extra, int slot, int& e, int& lo, int& hi) {
+__device__ __forceinline__ bool grouped_chunk(const int32_t* offs, int E, int extra, int slot, int& e, int& lo,
+                                              int& hi) {
   int skip = 0;   // chunks of the expert before this one
   if (slot >= extra) {
     e = slot - extra;
@@ -2138,9 +2138,9 @@ hipError_t launch_linear_mx8(int ydt, const uint8_t* spd, const uint8_t* sps, co
                              int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K, void* Y, int64_t ldy,
                              hipStream_t st);
 
-// spd (optional): the backbone's dense copy; used by the main kernel (K a
-// multiple of 128, M beyond the small-M kernel's range), which then skips the
-// expansion.
+// spd (optional): the backbone's dense copy; used by the main kernels (K a
+// multiple of 128, M beyond the small-M kernel's range), which then skip the
+// expansion, and by the small-M kernel when it is the only form.
 hipError_t launch_linear_mx(int pat, int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps,
                             const uint8_t* dnc, const uint8_t* dns, int64_t M, const uint8_t* wc, const uint8_t* ws,
                             int N, int K, void* Y, int64_t ldy, const uint8_t* spd, hipStream_t st) {
@@ -2168,8 +2168,8 @@ hipError_t launch_linear_mx(int pat, int ydt, const uint8_t* spc, const uint8_t*
 }
 
 template <int MF, int NB, int KS, int PAT>
-static hipError_t go_grouped_skinny(const SkinnyArgs& p, const int32_t* ridx, const int32_t* offs, int E, int64_t total, void* Y,
-                                    int ydt, int64_t ldy, hipStream_t st) {
+static hipError_t go_grouped_skinny(const SkinnyArgs& p, const int32_t* ridx, const int32_t* offs, int E,
+                                    int64_t total, void* Y, int ydt, int64_t ldy, hipStream_t st) {
   const int ncg = (p.N + 16 * NB - 1) / (16 * NB);
   const int extra = (int)(total / (16 * MF));
   const dim3 grid((unsigned)ncg * (unsigned)(E + extra)), block(64 * KS);
