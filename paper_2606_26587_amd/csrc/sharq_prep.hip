@@ -146,6 +146,44 @@ __global__ __launch_bounds__(256) void k_prep_blocks(XSrc src, int M, int K, Act
   }
 }
 
+// SiLU.mul input with few rows: a workgroup takes 64 of a panel's blocks; its
+// 256 threads form h eight values each and hand the blocks over in LDS, and the
+// first wavefront quantizes them as k_prep_blocks does.  With a block per
+// thread that kernel leaves the chip mostly idle there, and its time is the chain of
+// one thread's 32 SiLUs and the quantization behind them (K 14336, M 4: MXFP4
+// 7.1 us -> 3.8, NVFP4 with the launch that copies its scale 12.8 -> 9.5).
+template <int PAT, bool NV>
+__global__ __launch_bounds__(256) void k_prep_silu_few(XSrc src, int M, int K, ActOut o, const float* S_ptr) {
+  __shared__ uint4 h[64][5];   // a block's four pieces and 16 bytes that spread the banks
+  const int nblk = K / 32, p = blockIdx.y;
+  const uint32_t q = (uint32_t)min(4, nblk - 4 * p);   // blocks per row in this panel
+  const uint32_t n = q * (uint32_t)M, t0 = blockIdx.x * 64u;
+  {
+    const uint32_t l = threadIdx.x >> 2, c = threadIdx.x & 3u, t = t0 + l;
+    if (t < n) {
+      const uint32_t row = t / q, at = 4u * (4u * (uint32_t)p + (t - row * q)) + c;
+      const uint4 v = load_chunk<2>(src, (int64_t)row, at);
+      if (src.H != nullptr) reinterpret_cast<uint4*>(src.H + (int64_t)row * src.ldh)[at] = v;
+      h[l][c] = v;
+    }
+  }
+  __syncthreads();
+  const uint32_t t = t0 + threadIdx.x;
+  if (threadIdx.x >= 64 || t >= n) return;
+  const float S = NV ? *S_ptr : 1.0f, six_s = 6.0f * S;
+  uint4 xq[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) xq[j] = h[threadIdx.x][j];
+  float y[32];
+  unpack_bf16x32(xq, y);
+  const BlockOut d = block_at<NV>(o, (int64_t)p * M * 4 + t);
+  if (NV) {
+    block_nv<PAT>(y, S, six_s, d);
+  } else {
+    block_mx<PAT>(y, d, o.rule_bias);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // NVFP4 per-tensor scale (App. A.1.3): S = amax(y) / 2688 over the whole call,
 // 1 for an all-zero tensor.  A pre-pass leaves one partial maximum per
@@ -745,6 +783,25 @@ hipError_t launch_prep_hif4(const uint16_t* X, int M, int K, int64_t ldx, const 
   return hipGetLastError();
 }
 
+// Blocks up to which k_prep_silu_few prepares a SiLU.mul input.  Past that the
+// chip is full either way and the wavefronts that wait for the quantizing one
+// cost more than the shorter chain saves.  Measured, k_prep_blocks /
+// k_prep_silu_few, us (NVFP4 with its scale's copy launch): K 14336 NVFP4 M 4
+// 12.8 / 9.5, M 64 12.4 / 9.5, M 512 (229376 blocks) 22.9 / 21.8, M 1024 33.1 /
+// 34.0; K 4096 M 2048 (262144 blocks) 23.5 / 24.8; MXFP4 K 14336 M 4 7.1 / 3.8, M
+// 512 14.2 / 12.4, M 2048 40.1 / 41.1; K 4096 M 2048 14.8 / 14.6.
+constexpr int64_t kSiluFewBlocks = 240000;
+
+template <int PAT, bool NV>
+static void go_prep_silu(const XSrc& src, int M, int K, const ActOut& o, const float* S, hipStream_t st) {
+  const int nblk = K / 32;
+  const unsigned panels = (unsigned)((nblk + 3) / 4);
+  if ((int64_t)M * nblk <= kSiluFewBlocks)
+    k_prep_silu_few<PAT, NV><<<dim3((unsigned)((4 * (int64_t)M + 63) / 64), panels), 256, 0, st>>>(src, M, K, o, S);
+  else
+    k_prep_blocks<PAT, NV, 2><<<dim3((unsigned)((4 * (int64_t)M + 255) / 256), panels), 256, 0, st>>>(src, M, K, o, S);
+}
+
 // Preparation of the down projection's input with SiLU.mul fused in front:
 // h = bf16(SiLU(gate) * up), written to h (when not NULL) and prepared
 // without RMSNorm.  nv: NVFP4 with the per-tensor scale from ts_in or from
@@ -763,18 +820,10 @@ hipError_t launch_prep_silu(const uint16_t* gate, const uint16_t* up, uint16_t* 
       go_amax<2>(src, M, K, nullptr, 0.0f, dnc, ts_out, st);
     }
   }
-  const int nblk = K / 32;
-  const dim3 g2((unsigned)((4 * (int64_t)M + 255) / 256), (unsigned)((nblk + 3) / 4));
   const float* S = nv ? ts_out : nullptr;
-  if (nv) {
-    if (pat == 24) k_prep_blocks<24, true, 2><<<g2, 256, 0, st>>>(src, M, K, o, S);
-    else if (pat == 49) k_prep_blocks<49, true, 2><<<g2, 256, 0, st>>>(src, M, K, o, S);
-    else k_prep_blocks<48, true, 2><<<g2, 256, 0, st>>>(src, M, K, o, S);
-  } else {
-    if (pat == 24) k_prep_blocks<24, false, 2><<<g2, 256, 0, st>>>(src, M, K, o, S);
-    else if (pat == 49) k_prep_blocks<49, false, 2><<<g2, 256, 0, st>>>(src, M, K, o, S);
-    else k_prep_blocks<48, false, 2><<<g2, 256, 0, st>>>(src, M, K, o, S);
-  }
+  if (pat == 24) nv ? go_prep_silu<24, true>(src, M, K, o, S, st) : go_prep_silu<24, false>(src, M, K, o, S, st);
+  else if (pat == 49) nv ? go_prep_silu<49, true>(src, M, K, o, S, st) : go_prep_silu<49, false>(src, M, K, o, S, st);
+  else nv ? go_prep_silu<48, true>(src, M, K, o, S, st) : go_prep_silu<48, false>(src, M, K, o, S, st);
   return hipGetLastError();
 }
 

@@ -142,3 +142,31 @@ def test_silu_mul_prep_nv_dense_only(S, G, T, K, n, m, pairs):
     dev = L.act_to_device_layout(o)
     for name in ("sp_scale", "dn_codes", "dn_scale"):
         G.assert_bytes_equal(name, G.host(getattr(a, name)), dev[name])
+
+
+@pytest.mark.parametrize("T,K,n,m,pairs,fmt,strided", [
+    (1, 32, 2, 4, False, "mx", False),         # one block
+    (15, 96, 4, 8, False, "nv", True),         # one panel of 3 blocks a row, 45 of a workgroup's 64
+    (16, 128, 2, 4, False, "nv", False),       # exactly one workgroup's blocks
+    (17, 160, 4, 8, True, "mx", True),         # one row into the second workgroup, a last panel of one block
+    (4, 14336, 4, 8, True, "nv", True),
+    (64, 14336, 2, 4, False, "mx", True),
+])
+def test_silu_mul_few_rows(S, G, T, K, n, m, pairs, fmt, strided):
+    """Edges of the kernel for few rows: 64 blocks of a panel per workgroup."""
+    check_silu(S, G, T, K, n, m, fmt, pairs, f"few-T{T}K{K}", strided=strided, seed=T + K)
+
+
+def test_silu_mul_few_rows_in_place(S, G):
+    """h written over gate, on both sides of the line between the two kernels."""
+    for T, K in ((20, 416), (7600, 1024)):
+        say(f"[silu] in place T={T} K={K}")
+        gate, up = synth.activations(T, K, seed=3), synth.activations(T, K, seed=4)
+        g, u = G.dev_bf16(gate), G.dev_bf16(up)
+        a = S.sharq_prepare_silu_mul(g, u, 2, 4, "nv", h_out=g)
+        torch.cuda.synchronize()
+        o = O.prepare_silu_mul(gate, up, 2, 4, "nv")
+        G.assert_bytes_equal("h", G.host(g.view(torch.int16)).view(np.uint16), o["h"])
+        dev = L.act_to_device_layout(o)
+        for name in O.ACT_BUFFERS:
+            G.assert_bytes_equal(name, G.host(getattr(a, name)), dev[name])
