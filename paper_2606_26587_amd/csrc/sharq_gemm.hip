@@ -28,6 +28,7 @@
 // block.  Accumulator element r of lane l is output row
 // 8 (r / 4) + 4 (l / 32) + (r % 4), column l % 32.
 
+#include "sharq_plan.hpp"
 #include "sharq_tile.hpp"
 #include <type_traits>
 
@@ -2133,7 +2134,6 @@ static hipError_t go_dense_backbone(const uint8_t* spd, const uint8_t* sps, cons
 }
 
 // The 8-wavefront kernel on a dense backbone copy (sharq_mx8.hip).
-bool use_mx8(int64_t M, int N);
 hipError_t launch_linear_mx8(int ydt, const uint8_t* spd, const uint8_t* sps, const uint8_t* dnc, const uint8_t* dns,
                              int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K, void* Y, int64_t ldy,
                              hipStream_t st);
@@ -2147,7 +2147,7 @@ hipError_t launch_linear_mx(int pat, int ydt, const uint8_t* spc, const uint8_t*
   const bool sdw = K >= kBK;   // at least one full panel
   constexpr int NF = 8;
   if (spd && K % kBK == 0 && !use_skinny(M, N, K)) {
-    if (use_mx8(M, N)) return launch_linear_mx8(ydt, spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
+    if (use_mx8(M, N, device_cus())) return launch_linear_mx8(ydt, spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     if (ydt == 2) return go_dense_backbone<float>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     if (ydt == 1) return go_dense_backbone<_Float16>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     return go_dense_backbone<uint16_t>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);

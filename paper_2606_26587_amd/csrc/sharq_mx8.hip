@@ -16,13 +16,13 @@
 // 4096 52.4 -> 47.9 (NF 3: one round of 256 tiles); N 28672 219.9 -> 210.8; M 4096,
 // N 4096, K 4096 65.7 -> 59.7; M 2048, N 4096, K 14336 102.5, 111.3 here (NF 2).
 
+#include "sharq_plan.hpp"
 #include "sharq_tile.hpp"
 #include <type_traits>
 
 namespace sharq {
 
 constexpr int kT8 = 512;                          // threads
-constexpr int kRows8 = 256;                       // rows of a tile
 constexpr int kOp8 = 256 * 64;                    // one operand of a 128-position step: 256 rows x 64 bytes
 constexpr int kScale8 = 256 * 4;                  // its E8M0 scales
 constexpr int kStage8 = 3 * kOp8 + 3 * kScale8;   // backbone, residual, weight; their scales
@@ -226,28 +226,15 @@ __device__ __forceinline__ void tiles8(const Args8& p, OutT* Y, int64_t ldy, uin
   }
 }
 
-__device__ __forceinline__ void tile8_of(int u, int gx, int gy, int& mt, int& nt) {
-  const int g = u / (4 * gx), first = 4 * g;
-  const int gs = gy - first < 4 ? gy - first : 4;
-  const int in = u - g * 4 * gx;
-  mt = first + in % gs;
-  nt = in / gs;
-}
-
 template <typename OutT, int NF>
 __global__ __launch_bounds__(kT8) void k_linear_mx8(Args8 p, OutT* Y, int64_t ldy, int gx, int gy, int full) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[kLds8];
-  const int per = (full + 7) >> 3;
   int id = (int)blockIdx.x;
-  tiles8<OutT, NF>(p, Y, ldy, lds, [&](Tile8& t) {   // each XCD (id mod 8) takes a contiguous range of tiles
-    int u = full;
-    while (u >= full) {
-      if (id >= 8 * per) return false;
-      u = (id & 7) * per + (id >> 3);
-      id += (int)gridDim.x;
-    }
+  tiles8<OutT, NF>(p, Y, ldy, lds, [&](Tile8& t) {
+    if (id >= full) return false;
     int mt, nt;
-    tile8_of(u, gx, gy, mt, nt);
+    tile_in_groups(xcd_unit(id, full), gx, gy, mt, nt);
+    id += (int)gridDim.x;
     t.row_lo = (int64_t)mt * kRows8;
     t.n0 = nt * 64 * NF;
     return true;
@@ -257,7 +244,7 @@ __global__ __launch_bounds__(kT8) void k_linear_mx8(Args8 p, OutT* Y, int64_t ld
     tiles8<OutT, 2>(p, Y, ldy, lds, [&](Tile8& t) {
       for (; u < 2 * (gx * gy - full); u += (int)gridDim.x) {
         int mt, nt;
-        tile8_of(full + (u >> 1), gx, gy, mt, nt);
+        tile_in_groups(full + (u >> 1), gx, gy, mt, nt);
         t.n0 = nt * 256 + 128 * (u & 1);
         if (t.n0 >= p.N) continue;
         t.row_lo = (int64_t)mt * kRows8;
@@ -269,45 +256,9 @@ __global__ __launch_bounds__(kT8) void k_linear_mx8(Args8 p, OutT* Y, int64_t ld
   }
 }
 
-// Launch plan: NF 4 or 3, and whole 256-column tiles (of a last round at most
-// half full, tiles run as halves).  us: the estimate per K step, rounds of
-// tiles over the CUs times the tile's measured step (1.85, 1.50, and 1.05 for a
-// half tile); 128-column tiles alone were never the best.
-struct Plan8 {
-  int nf, gx, gy, full, grid;
-  double us;
-};
-
-static Plan8 plan8(int64_t M, int N) {
-  const int cus = device_cus(), gy = (int)((M + kRows8 - 1) / kRows8);
-  Plan8 best{};
-  for (int nf = 4; nf >= 3; --nf) {
-    const int gx = (N + 64 * nf - 1) / (64 * nf);
-    const int64_t tiles = (int64_t)gx * gy, r = tiles % cus;
-    Plan8 p{nf, gx, gy, (int)tiles, (int)(tiles < cus ? tiles : cus), 0.0};
-    p.us = (double)((tiles + cus - 1) / cus) * (nf == 4 ? 1.85 : 1.50);
-    if (nf == 4 && tiles > cus && r > 0 && 2 * r <= cus) {
-      p.full = (int)(tiles - r);
-      p.us = (double)(tiles / cus) * 1.85 + 1.05;
-    }
-    if (best.nf == 0 || p.us < best.us) best = p;
-  }
-  return best;
-}
-
-// Whether this kernel's estimate is below that of the 4-wavefront one (rounds
-// of 128 x 256 tiles at 0.97 us a step, half tiles at 0.85).
-bool use_mx8(int64_t M, int N) {
-  const int cus = device_cus();
-  const int64_t tiles = ((M + 127) / 128) * (int64_t)((N + 255) / 256), r = tiles % cus;
-  if (tiles <= cus) return false;   // one round there: a tile of half the size ends sooner
-  const double old_us = (double)(tiles / cus) * 0.97 + (r == 0 ? 0.0 : 2 * r <= cus ? 0.85 : 0.97);
-  return plan8(M, N).us < 0.98 * old_us;
-}
-
 template <typename OutT>
 static hipError_t go8(const Args8& a, void* Y, int64_t ldy, hipStream_t st) {
-  const Plan8 p = plan8(a.M, a.N);
+  const Plan8 p = plan8(a.M, a.N, device_cus());
   OutT* y = reinterpret_cast<OutT*>(Y);
   const dim3 grid((unsigned)p.grid), block(kT8);
   if (p.nf == 4) k_linear_mx8<OutT, 4><<<grid, block, 0, st>>>(a, y, ldy, p.gx, p.gy, p.full);

@@ -1,0 +1,72 @@
+// Numbering of the tiles that the persistent GEMM kernels walk, and the plans
+// of their launches.  Plain C++ (constexpr functions run on both sides), so
+// that a host test can replay a launch.
+#pragma once
+
+#include <stdint.h>
+
+namespace sharq {
+
+// Unit of id in [0, units): one to one onto [0, units), the ids of each XCD
+// (workgroups are dealt round-robin, id mod 8) taking a contiguous range.  A
+// workgroup b of G walks the ids b, b + G, ...: no id is without a unit, so
+// none gets more than ceil(units / G).  (With equal ranges of ceil(units / 8)
+// ids past the last workgroup held units where units < G was not a multiple of
+// 8, and a launch of one round ran two.)
+constexpr int xcd_unit(int id, int units) {
+  const int x = id & 7, q = units >> 3, rem = units & 7;
+  return x * q + (x < rem ? x : rem) + (id >> 3);
+}
+
+// Tile u of a grid of gx by gy: groups of 4 row tiles, column by column, so
+// that 32 consecutive tiles (the workgroups of one XCD) are 4 by 8.
+constexpr void tile_in_groups(int u, int gx, int gy, int& mt, int& nt) {
+  const int g = u / (4 * gx), first = 4 * g;
+  const int gs = gy - first < 4 ? gy - first : 4;
+  const int in = u - g * 4 * gx;
+  mt = first + in % gs;
+  nt = in / gs;
+}
+
+// ---------------------------------------------------------------------------
+// MXFP4 on the dense backbone copy, 256 rows x 64 NF columns (k_linear_mx8)
+// ---------------------------------------------------------------------------
+
+constexpr int kRows8 = 256;   // rows of a tile
+
+// Launch plan: NF 4 or 3, and whole 256-column tiles (of a last round at most
+// half full, tiles run as halves).  us: the estimate per K step, rounds of
+// tiles over the CUs times the tile's measured step (1.85, 1.50, and 1.05 for a
+// half tile); 128-column tiles alone were never the best.
+struct Plan8 {
+  int nf, gx, gy, full, grid;
+  double us;
+};
+
+constexpr Plan8 plan8(int64_t M, int N, int cus) {
+  const int gy = (int)((M + kRows8 - 1) / kRows8);
+  Plan8 best{};
+  for (int nf = 4; nf >= 3; --nf) {
+    const int gx = (N + 64 * nf - 1) / (64 * nf);
+    const int64_t tiles = (int64_t)gx * gy, r = tiles % cus;
+    Plan8 p{nf, gx, gy, (int)tiles, (int)(tiles < cus ? tiles : cus), 0.0};
+    p.us = (double)((tiles + cus - 1) / cus) * (nf == 4 ? 1.85 : 1.50);
+    if (nf == 4 && tiles > cus && r > 0 && 2 * r <= cus) {
+      p.full = (int)(tiles - r);
+      p.us = (double)(tiles / cus) * 1.85 + 1.05;
+    }
+    if (best.nf == 0 || p.us < best.us) best = p;
+  }
+  return best;
+}
+
+// Whether that kernel's estimate is below that of the 4-wavefront one (rounds
+// of 128 x 256 tiles at 0.97 us a step, half tiles at 0.85).
+constexpr bool use_mx8(int64_t M, int N, int cus) {
+  const int64_t tiles = ((M + 127) / 128) * (int64_t)((N + 255) / 256), r = tiles % cus;
+  if (tiles <= cus) return false;   // one round there: a tile of half the size ends sooner
+  const double old_us = (double)(tiles / cus) * 0.97 + (r == 0 ? 0.0 : 2 * r <= cus ? 0.85 : 0.97);
+  return plan8(M, N, cus).us < 0.98 * old_us;
+}
+
+}  // namespace sharq
