@@ -7,6 +7,7 @@
 // in the epilogue.  K a multiple of 128 runs on the persistent kernel below in
 // fp16; other K on a double-buffered one in bf16.
 
+#include "sharq_plan.hpp"
 #include "sharq_tile.hpp"
 #include <type_traits>
 
@@ -186,7 +187,6 @@ __global__ __launch_bounds__(256) void k_linear_nv(const uint8_t* sp_codes, cons
 
 constexpr int kFmtNv = 0, kFmtHf = 1;
 constexpr int kT16 = 512;                     // threads
-constexpr int kRows16 = 256;                  // rows of a tile
 constexpr int kPart16 = 256 * 64;             // one operand of a step: 256 rows x 32 positions x 2 bytes
 constexpr int kStage16 = 3 * kPart16;         // activation (merged, or backbone), weight, residual
 constexpr int kLds16 = 3 * kStage16;          // 144 KB; the epilogue reuses it
@@ -541,16 +541,6 @@ __device__ __forceinline__ void tile16(const Args16& p, OutT* Y, int64_t ldy, in
     il_epilogue<OutT, NF>(acc[r], Y, ldy, row_lo, row_hi, n0 + wn * 32 * NF, p.N, epi, 2 * wm + r, lane);
 }
 
-// Tile u of a grid of gx by gy: groups of 4 row tiles, column by column, so
-// that 32 consecutive tiles (the workgroups of one XCD) are 4 by 8.
-__device__ __forceinline__ void tile16_of(int u, int gx, int gy, int& mt, int& nt) {
-  const int g = u / (4 * gx), first = 4 * g;
-  const int gs = gy - first < 4 ? gy - first : 4;
-  const int in = u - g * 4 * gx;
-  mt = first + in % gs;
-  nt = in / gs;
-}
-
 // At most one workgroup per CU walks the units b, b + G, ....  Units [0, full)
 // are whole tiles, each XCD (id mod 8) taking a contiguous range of them; with
 // NF 4 the rest run as two half tiles of 128 columns each.
@@ -558,19 +548,16 @@ template <int FMT, int PAT, typename OutT, int NF>
 __global__ __launch_bounds__(kT16) void k_linear16(Args16 p, OutT* Y, int64_t ldy, int gx, int gy, int full) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[kLds16];
   __shared__ uint32_t flags[24];
-  const int per = (full + 7) >> 3;
-  for (int id = (int)blockIdx.x; id < 8 * per; id += (int)gridDim.x) {
-    const int u = (id & 7) * per + (id >> 3);
-    if (u >= full) continue;   // uniform across the workgroup
+  for (int id = (int)blockIdx.x; id < full; id += (int)gridDim.x) {
     int mt, nt;
-    tile16_of(u, gx, gy, mt, nt);
+    tile_in_groups(xcd_unit(id, full), gx, gy, mt, nt);
     tile16<FMT, PAT, OutT, NF>(p, Y, ldy, (int64_t)mt * kRows16, nt * 64 * NF, lds, flags);
     __syncthreads();   // the LDS is free before the next tile's prologue
   }
   if constexpr (NF == 4) {
     for (int u = (int)blockIdx.x; u < 2 * (gx * gy - full); u += (int)gridDim.x) {
       int mt, nt;
-      tile16_of(full + (u >> 1), gx, gy, mt, nt);
+      tile_in_groups(full + (u >> 1), gx, gy, mt, nt);
       const int n0 = nt * 256 + 128 * (u & 1);
       if (n0 < p.N) tile16<FMT, PAT, OutT, 2>(p, Y, ldy, (int64_t)mt * kRows16, n0, lds, flags);
       __syncthreads();
@@ -578,42 +565,9 @@ __global__ __launch_bounds__(kT16) void k_linear16(Args16 p, OutT* Y, int64_t ld
   }
 }
 
-// Tile width and whole tiles of a launch.  A tile of 64 NF columns takes about
-// (NF + 1) / 5 of a 256-column one (its activation work does not shrink with
-// it; NVFP4 0.63, 0.93 and 1.10 us a step for NF 2, 3 and 4), and the launch as long as its rounds of tiles over the CUs: the
-// cheapest width wins, the wider of equals.  A last round of 256-column tiles
-// that is at most half full runs as half tiles.
-struct Plan16 {
-  int nf, gx, gy, full, grid;
-  int64_t cost;   // in fifths of a whole 256-column tile
-};
-
-static Plan16 plan16(int64_t M, int N) {
-  const int cus = device_cus(), gy = (int)((M + kRows16 - 1) / kRows16);
-  Plan16 best{};
-  int64_t least = 0;
-  for (int nf = 4; nf >= 2; --nf) {
-    const int gx = (N + 64 * nf - 1) / (64 * nf);
-    const int64_t tiles = (int64_t)gx * gy, r = tiles % cus;
-    int64_t cost = (tiles + cus - 1) / cus * (nf + 1);
-    Plan16 p{nf, gx, gy, (int)tiles, (int)(tiles < cus ? tiles : cus), 0};
-    if (nf == 4 && tiles > cus && r > 0 && 2 * r <= cus) {
-      p.full = (int)(tiles - r);
-      cost = tiles / cus * 5 + 3;
-    }
-    if (least == 0 || cost < least) {
-      best = p;
-      best.cost = least = cost;
-    }
-  }
-  return best;
-}
-
-int64_t linear16_cost(int64_t M, int N) { return plan16(M, N).cost; }
-
 template <int FMT, int PAT, typename OutT>
 static hipError_t go_linear16(const Args16& a, void* Y, int64_t ldy, hipStream_t st) {
-  const Plan16 p = plan16(a.M, a.N);
+  const Plan16 p = plan16(a.M, a.N, device_cus());
   OutT* y = reinterpret_cast<OutT*>(Y);
   const dim3 grid((unsigned)p.grid), block(kT16);
   if (p.nf == 4) k_linear16<FMT, PAT, OutT, 4><<<grid, block, 0, st>>>(a, y, ldy, p.gx, p.gy, p.full);

@@ -21,6 +21,7 @@
 // Any K the formats allow: in a last panel narrower than 128, lanes whose
 // block lies past K reread block 0 and zero its weight codes.
 
+#include "sharq_plan.hpp"
 #include "sharq_tile.hpp"
 
 namespace sharq {
@@ -245,8 +246,6 @@ static S16Cfg s16_config(bool nv, int64_t M, int N, int K) {
   return {mf, nb, ks};
 }
 
-int64_t linear16_cost(int64_t M, int N);   // the prefill kernel's plan (sharq_linear16.hip)
-
 // Up to 32 rows always (the layer streams its weight); above, where the
 // estimate of this kernel's time is below the prefill kernel's.  This
 // kernel's grows with the padded work, 5 (NVFP4) or 11 (HiF4) us per 1e9 M N
@@ -263,7 +262,7 @@ bool use_skinny16(bool nv, int64_t M, int N, int K) {
   const int64_t rows = (M + 15) / 16 * 16, cols = (N + 15) / 16 * 16;
   double main_us;   // per 32 positions
   if (K % 128 == 0) {
-    main_us = (double)linear16_cost(M, N) * (nv ? 0.21 : 0.38);
+    main_us = (double)plan16(M, N, device_cus()).cost * (nv ? 0.21 : 0.38);
   } else {
     const int64_t tiles = ((M + 127) / 128) * ((int64_t)(N + 255) / 256), cus = device_cus();
     main_us = (double)((tiles + cus - 1) / cus) * (nv ? 0.69 : 1.93);

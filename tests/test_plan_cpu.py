@@ -21,6 +21,10 @@ void plan_mx8(int64_t M, int N, int cus, int* out) {
   const Plan8 p = plan8(M, N, cus);
   out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid;
 }
+void plan_16(int64_t M, int N, int cus, int* out) {
+  const Plan16 p = plan16(M, N, cus);
+  out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid;
+}
 // row and column tile of every id in [0, units)
 void walk(int units, int gx, int gy, int* mt, int* nt) {
   for (int id = 0; id < units; ++id) tile_in_groups(xcd_unit(id, units), gx, gy, mt[id], nt[id]);
@@ -37,7 +41,8 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I",
                     os.path.join(ROOT, "paper_2606_26587_amd", "csrc"), str(d / "shim.cpp"), "-o", so], check=True)
     L = ctypes.CDLL(so)
-    L.plan_mx8.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
+    for f in (L.plan_mx8, L.plan_16):
+        f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
     return L
 
 
@@ -55,7 +60,7 @@ def rounds_of(L, units, gx, gy, grid):
     return int(np.bincount(np.arange(units) % grid, minlength=grid).max())
 
 
-@pytest.mark.parametrize("name", ["plan_mx8"])
+@pytest.mark.parametrize("name", ["plan_mx8", "plan_16"])
 @pytest.mark.parametrize("cus", [256, 64, 38])
 def test_rounds(plan, name, cus):
     out = (ctypes.c_int * 5)()
