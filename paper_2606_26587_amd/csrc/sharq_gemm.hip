@@ -35,7 +35,6 @@
 namespace sharq {
 
 constexpr int kLdsStride = 80;    // bytes per staged weight row (64 + 16 to spread LDS banks)
-constexpr int kSkinnyMaxM = 32;   // activation rows up to which the small-M kernel runs
 
 __device__ __forceinline__ v8i as_operand(uint4 q) {
   v8i v;
@@ -1365,15 +1364,50 @@ __device__ __forceinline__ void skinny_compute(const SkinnyArgs& p, const int64_
 #pragma unroll
     for (int n = 0; n < NB; ++n) acc[m][n] = v4f_t{0.0f, 0.0f, 0.0f, 0.0f};
 
+  // The order of a panel's loads and MFMAs.  Left alone, the compiler moves both
+  // stages' conditional loads behind both stages' MFMAs and then waits for all of
+  // them, which suits few rows (more wavefronts stream); with 64 rows a CU has one
+  // wavefront per SIMD and its own MFMAs have to cover its loads.  Fences keep them
+  // between; with the backbone to expand, loads without a branch (past the
+  // range the last panel again) do better.  N 4096, K 14336, M 256, us: dense copy
+  // 42.0 plain, 43.0 clamped, 36.8 fenced; 2:4 54.1, 40.3, 49.6; 4:8 75.1, 62.5, 73.3.
+  constexpr int kPlain = 0, kFenced = 1, kClamped = 2;
+  constexpr int kOrder = MF == 4 && PAT == 0 ? kFenced : PAT != 0 && NB == 4 && MF * KS >= 16 ? kClamped : kPlain;
   SkinnyStage<MF, NB> s0, s1;
   if (k0 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, row, n0, k0, lane);
   if (k0 + 1 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, row, n0, k0 + 1, lane);
   int ks = k0;
-  for (; ks + 1 < k1; ks += 2) {
-    skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
-    if (ks + 2 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, row, n0, ks + 2, lane);
-    skinny_step<MF, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
-    if (ks + 3 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, row, n0, ks + 3, lane);
+  if constexpr (kOrder == kFenced) {
+    for (; ks + 1 < k1; ks += 2) {
+      skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
+      SHARQ_FENCE();
+      if (ks + 2 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, row, n0, ks + 2, lane);
+      SHARQ_FENCE();
+      skinny_step<MF, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
+      SHARQ_FENCE();
+      if (ks + 3 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, row, n0, ks + 3, lane);
+      SHARQ_FENCE();
+    }
+  } else if constexpr (kOrder == kClamped) {
+    constexpr int kMore = MF == 2 && !RAG ? 2 : 1;   // 2: no loads after the last panels
+    for (; ks + kMore < k1; ks += 2) {
+      skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
+      skinny_load<MF, NB, PAT, RAG>(s0, p, row, n0, min(ks + 2, k1 - 1), lane);
+      skinny_step<MF, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
+      skinny_load<MF, NB, PAT, RAG>(s1, p, row, n0, min(ks + 3, k1 - 1), lane);
+    }
+    if (kMore == 2 && ks + 1 < k1) {
+      skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
+      skinny_step<MF, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
+      ks += 2;
+    }
+  } else {
+    for (; ks + 1 < k1; ks += 2) {
+      skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
+      if (ks + 2 < k1) skinny_load<MF, NB, PAT, RAG>(s0, p, row, n0, ks + 2, lane);
+      skinny_step<MF, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
+      if (ks + 3 < k1) skinny_load<MF, NB, PAT, RAG>(s1, p, row, n0, ks + 3, lane);
+    }
   }
   if (ks < k1) skinny_step<MF, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
 
@@ -1553,26 +1587,6 @@ static int skinny_split(int wgs, int K, int cap) {
   return ks;
 }
 
-// Above 32 rows the workgroups tile M as well.  Each configuration's time is
-// that of one workgroup (us at K = 4096, measured with one per CU) times the
-// rounds of workgroups over the CUs; the cheapest runs.
-struct SkinnyWide {
-  int mf, nb, ks;
-  double us_4096;
-};
-
-static SkinnyWide skinny_wide(int64_t M, int N) {
-  constexpr SkinnyWide cfgs[5] = {{1, 1, 8, 1.8}, {2, 1, 8, 3.2}, {2, 2, 8, 4.2}, {2, 4, 8, 6.2}, {4, 4, 4, 11.5}};
-  const int cus = device_cus();
-  SkinnyWide best{};
-  for (const SkinnyWide& c : cfgs) {
-    const int64_t wgs = (int64_t)((N + 16 * c.nb - 1) / (16 * c.nb)) * ((M + 16 * c.mf - 1) / (16 * c.mf));
-    const double us = c.us_4096 * (double)((wgs + cus - 1) / cus);
-    if (best.mf == 0 || us < best.us_4096) best = {c.mf, c.nb, c.ks, us};
-  }
-  return best;
-}
-
 // (row fragments, column fragments, K splits) by M: every activation block
 // expansion feeds NB column fragments; the K split keeps enough wavefronts
 // streaming the weight.  Above 16 rows the workgroups tile M by 32 or 64.
@@ -1608,31 +1622,14 @@ static hipError_t go_skinny_m(const SkinnyArgs& p, void* Y, int ydt, int64_t ldy
     return ks == 8 ? go_skinny<2, 2, 8, PAT>(p, Y, ydt, ldy, st)
                    : go_skinny<2, 2, 4, PAT>(p, Y, ydt, ldy, st);
   }
-  const SkinnyWide w = skinny_wide(M, N);
+  const SkinnyWide w = skinny_wide(M, N, K, backbone_form(PAT), device_cus());
 #define SHARQ_SKINNY(MF_, NB_, KS_) \
   if (w.mf == MF_ && w.nb == NB_ && w.ks == KS_) return go_skinny<MF_, NB_, KS_, PAT>(p, Y, ydt, ldy, st);
-  SHARQ_SKINNY(1, 1, 8) SHARQ_SKINNY(2, 1, 8) SHARQ_SKINNY(2, 2, 8) SHARQ_SKINNY(2, 4, 8) SHARQ_SKINNY(4, 4, 4)
+  SHARQ_SKINNY(1, 1, 8) SHARQ_SKINNY(2, 1, 8) SHARQ_SKINNY(2, 2, 8) SHARQ_SKINNY(2, 4, 8) SHARQ_SKINNY(2, 4, 4)
+  SHARQ_SKINNY(4, 4, 4)
 #undef SHARQ_SKINNY
   return hipErrorInvalidValue;   // unreachable
 }
-
-// The small-M kernel serves M <= 32, and larger M where its estimate is 15%
-// below the main kernel's (3 us and, per round of 128 x 256 tiles over the CUs,
-// 0.6 us a panel, up to 1.5 times that with every CU running).  Measured,
-// small-M / main kernel, us: N 1024 K 4096 M 256 6.7 / 23, M 1024 15 / 23; N 6144 K
-// 4096 M 96 14 / 23, M 160 16 / 23, M 256 24 / 23, M 512 39 / 24; N 4096 K 14336 M
-// 256 35 / 68, M 512 67 / 70; N 28672 K 4096 M 48 30 / 24; N 2048 K 2048 M 512 9.9 /
-// 14, M 768 15 / 14.
-static bool use_skinny(int64_t M, int N, int K) {
-  if (K < kBK) return false;
-  if (M <= kSkinnyMaxM) return true;
-  if (M > 4096) return false;
-  const int64_t tiles = ((M + kBM - 1) / kBM) * (int64_t)((N + 255) / 256), cus = device_cus();
-  const double rounds = (double)((tiles + cus - 1) / cus), fill = tiles < cus ? (double)tiles / (double)cus : 1.0;
-  const double main_us = 3.0 + 0.6 * K / 128.0 * rounds * (1.0 + 0.5 * fill);
-  return 1.15 * (2.5 + skinny_wide(M, N).us_4096 * K / 4096.0) < main_us;
-}
-
 
 // ---------------------------------------------------------------------------
 // Path combinations (Sec. 4.4, table "ablation-combination"): the sum of up
@@ -2146,13 +2143,15 @@ hipError_t launch_linear_mx(int pat, int ydt, const uint8_t* spc, const uint8_t*
                             int N, int K, void* Y, int64_t ldy, const uint8_t* spd, hipStream_t st) {
   const bool sdw = K >= kBK;   // at least one full panel
   constexpr int NF = 8;
-  if (spd && K % kBK == 0 && !use_skinny(M, N, K)) {
+  const bool dense = spd && K % kBK == 0;
+  const bool skinny = use_skinny(M, N, K, backbone_form(spc ? pat : 0), backbone_form(dense ? 0 : pat), device_cus());
+  if (dense && !skinny) {
     if (use_mx8(M, N, device_cus())) return launch_linear_mx8(ydt, spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     if (ydt == 2) return go_dense_backbone<float>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     if (ydt == 1) return go_dense_backbone<_Float16>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
     return go_dense_backbone<uint16_t>(spd, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);
   }
-  if (use_skinny(M, N, K)) {
+  if (skinny) {
     if (spc == nullptr)   // the backbone exists as its dense copy only
       return go_skinny_m<0>(SkinnyArgs{spd, nullptr, sps, dnc, dns, wc, ws, M, N, K}, Y, ydt, ldy, st);
     const SkinnyArgs p{spc, spm, sps, dnc, dns, wc, ws, M, N, K};

@@ -71,6 +71,66 @@ constexpr bool use_mx8(int64_t M, int N, int cus) {
 }
 
 // ---------------------------------------------------------------------------
+// MXFP4 with few rows (k_linear_mx_skinny)
+// ---------------------------------------------------------------------------
+
+// What a kernel reads as backbone: the dense copy, 2:4 or 4:8 compressed.
+constexpr int backbone_form(int pat) { return pat == 0 ? 0 : pat == 24 ? 1 : 2; }
+
+// Above 32 rows the workgroups tile M as well: 16 mf rows and 16 nb columns, K
+// over ks wavefronts.  A launch takes us[0] + us[1] (R - 1) + us[2] R K / 4096,
+// R the rounds of workgroups over the CUs, by the backbone's form.  Fitted to
+// about 300 shapes per form with the weight streamed from HBM (N 512 to 28672, K
+// 768 to 18944, M 33 to 4096; nine in ten within 6 to 20%).  The forms differ, and
+// so does what a round costs beside its share of K: with neither in the
+// estimate, 160 x 7168 x 2048 4:8 took 22.2 us here and 18.0 on the main kernel.
+struct SkinnyCfg {
+  int mf, nb, ks;
+  double us[3][3];
+};
+constexpr SkinnyCfg kSkinnyCfg[6] = {
+    {1, 1, 8, {{2.57, 0.16, 2.04}, {2.83, 0.31, 2.31}, {2.96, 0.38, 3.52}}},
+    {2, 1, 8, {{2.46, 0.93, 3.64}, {2.89, 0.65, 4.50}, {3.02, 1.33, 7.51}}},
+    {2, 2, 8, {{2.68, 1.35, 4.45}, {3.15, 1.53, 5.30}, {3.34, 1.65, 8.20}}},
+    {2, 4, 8, {{3.19, 1.93, 5.93}, {3.80, 2.11, 6.33}, {4.23, 2.46, 8.53}}},
+    {4, 4, 4, {{5.80, 4.99, 8.41}, {6.67, 5.13, 9.20}, {7.27, 5.44, 15.6}}},
+    {2, 4, 4, {{4.17, 0.66, 5.59}, {4.76, 0.82, 6.63}, {4.72, 2.97, 9.73}}},
+};
+
+struct SkinnyWide {
+  int mf, nb, ks;
+  double us;
+};
+
+constexpr SkinnyWide skinny_wide(int64_t M, int N, int K, int form, int cus) {
+  SkinnyWide best{};
+  for (const SkinnyCfg& c : kSkinnyCfg) {
+    // its ragged form needs the registers of two wavefronts: 22 us, 12 in the estimate, at 256 x 5000 x 2080
+    if (K % 128 != 0 && c.mf == 2 && c.nb == 4 && c.ks == 4) continue;
+    const int64_t wgs = ((int64_t)N + 16 * c.nb - 1) / (16 * c.nb) * ((M + 16 * c.mf - 1) / (16 * c.mf));
+    const double r = (double)((wgs + cus - 1) / cus);
+    const double us = c.us[form][0] + c.us[form][1] * (r - 1.0) + c.us[form][2] * r * K / 4096.0;
+    if (best.mf == 0 || us < best.us) best = {c.mf, c.nb, c.ks, us};
+  }
+  return best;
+}
+
+// The small-M kernel serves M <= 32, and larger M where its estimate is 5%
+// below the main kernel's: a start, and per panel and round of 128 x 256 tiles
+// over the CUs a share that grows with the CUs at work (same shapes; nine in ten
+// within 3 to 6%).  form, main_form: what each of the two would read.
+constexpr bool use_skinny(int64_t M, int N, int K, int form, int main_form, int cus) {
+  constexpr double kMain[3][3] = {{5.19, 0.553, 0.183}, {5.73, 0.686, 0.163}, {6.51, 0.709, 0.176}};
+  if (K < 128) return false;
+  if (M <= 32) return true;
+  if (M > 4096) return false;
+  const int64_t tiles = ((M + 127) / 128) * (((int64_t)N + 255) / 256);
+  const double rounds = (double)((tiles + cus - 1) / cus), fill = tiles < cus ? (double)tiles / (double)cus : 1.0;
+  const double main_us = kMain[main_form][0] + K / 128.0 * rounds * (kMain[main_form][1] + kMain[main_form][2] * fill);
+  return 1.05 * skinny_wide(M, N, K, form, cus).us < main_us;
+}
+
+// ---------------------------------------------------------------------------
 // NVFP4 and HiF4 at prefill sizes, 256 rows x 64 NF columns (k_linear16)
 // ---------------------------------------------------------------------------
 

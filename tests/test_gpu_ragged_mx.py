@@ -57,6 +57,29 @@ def test_ragged_linear(S, G, n, m, T, N, K):
     assert torch.equal(y16, y[:T, :N].to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("T,N,K,n,m,dense", [
+    (97, 4100, 2176, 2, 4, True), (128, 4100, 2048, 4, 8, True),            # 64-row tiles, dense copy: 5 + 2 and 4 panels
+    (97, 4100, 2080, 2, 4, False), (97, 4100, 2176, 4, 8, False),           # compressed, ragged and whole panels
+    (130, 2000, 416, 2, 4, False), (300, 1000, 416, 4, 8, False),           # 32 rows, K over 8: one panel each or none
+    (100, 4100, 1280, 2, 4, True), (130, 4100, 512, 2, 4, False),           # 32 rows, K over 4
+])
+def test_row_tiles(S, G, T, N, K, n, m, dense):
+    """Above 32 rows: each order of loads and MFMAs of the small-M kernel, with panel counts per
+    wavefront that are odd, even, one and none."""
+    o = O.prepare(synth.activations(T, K, seed=T + N), synth.gamma(K, seed=3), 1e-6, n, m, "mx")
+    wo = O.quantize_weight(synth.weight(N, K, seed=7), "mx")
+    a, w = G.oracle_to_act(o, dense_backbone=dense), G.oracle_to_weight(wo)
+    if dense:
+        a.sp_codes = a.sp_meta = None
+    y = torch.full((T + 1, N + 3), float("nan"), dtype=torch.float32, device="cuda")
+    S.sharq_linear(a, w, out=y[:T, :N])
+    torch.cuda.synchronize()
+    got = G.host(y)
+    assert np.isnan(got[T]).all() and np.isnan(got[:, N:]).all(), "written outside the output"
+    rows = np.unique(np.concatenate([np.arange(0, T, 7), np.arange(T - 5, T)]))
+    within(got[rows, :N], O.linear(o, wo, rows=rows), O.linear_abs(o, wo, rows=rows), K)
+
+
 @pytest.mark.parametrize("gather", [True, False])
 @pytest.mark.parametrize("N,K", [(328, 416), (201, 416), (201, 544), (130, 96)])
 def test_ragged_grouped(S, G, gather, N, K):

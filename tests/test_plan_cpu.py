@@ -25,6 +25,11 @@ void plan_16(int64_t M, int N, int cus, int* out) {
   const Plan16 p = plan16(M, N, cus);
   out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid;
 }
+// {small-M kernel or not, mf, nb, ks of its configuration above 32 rows}
+void plan_skinny(int64_t M, int N, int K, int form, int cus, int* out) {
+  const SkinnyWide w = skinny_wide(M, N, K, form, cus);
+  out[0] = use_skinny(M, N, K, form, form, cus), out[1] = w.mf, out[2] = w.nb, out[3] = w.ks;
+}
 // row and column tile of every id in [0, units)
 void walk(int units, int gx, int gy, int* mt, int* nt) {
   for (int id = 0; id < units; ++id) tile_in_groups(xcd_unit(id, units), gx, gy, mt[id], nt[id]);
@@ -43,6 +48,7 @@ def plan(tmp_path_factory):
     L = ctypes.CDLL(so)
     for f in (L.plan_mx8, L.plan_16):
         f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
+    L.plan_skinny.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     return L
 
 
@@ -74,3 +80,40 @@ def test_rounds(plan, name, cus):
         rest = gx * gy - full   # a last round of half tiles
         assert rest == 0 or (nf == 4 and full % cus == 0 and 2 * rest <= grid)
     assert odd > 20   # tile counts that are no multiple of 8 are among them
+
+
+DENSE, C24, C48 = 0, 1, 2
+
+
+@pytest.mark.parametrize("form,M,N,K,small", [
+    # (us on one card, the weight streamed: small-M kernel / main kernel)
+    (DENSE, 64, 18944, 1024, False),     # 11.7 / 10.0
+    (DENSE, 768, 2048, 768, False),      # 9.7 / 8.8
+    (C48, 192, 7168, 2048, False),       # 22.5 / 18.1
+    (C48, 768, 2048, 768, False),        # 13.0 / 10.8
+    (C48, 48, 18944, 3584, False),       # 35.8 / 26.6
+    (C24, 320, 4096, 14336, True),       # 79.5 / 84.6
+    (C48, 96, 4096, 4096, True),         # 13.0 / 28.8
+    (DENSE, 256, 4096, 14336, True),     # 36.8 / 70.6
+    (DENSE, 512, 1024, 4096, True),      # 9.3 / 23.2
+    (DENSE, 32, 28672, 4096, True), (C48, 1, 64, 128, True),    # up to 32 rows always
+    (DENSE, 2048, 4096, 4096, False), (C24, 33, 64, 96, False), (DENSE, 5000, 64, 128, False),
+])
+def test_small_m_choice(plan, form, M, N, K, small):
+    out = (ctypes.c_int * 4)()
+    plan.plan_skinny(M, N, K, form, 256, out)
+    assert bool(out[0]) == small, (M, N, K)
+
+
+@pytest.mark.parametrize("form,M,N,K,cfg", [
+    # 37 us; 42 and more with the other configurations
+    (DENSE, 192, 4096, 14336, (4, 4, 4)), (DENSE, 256, 4096, 14336, (4, 4, 4)),
+    # what tests/test_gpu_ragged_mx.py::test_row_tiles runs
+    (DENSE, 97, 4100, 2176, (4, 4, 4)), (DENSE, 128, 4100, 2048, (4, 4, 4)), (DENSE, 100, 4100, 1280, (2, 4, 4)),
+    (C24, 97, 4100, 2080, (4, 4, 4)), (C24, 130, 2000, 416, (2, 4, 8)), (C24, 130, 4100, 512, (2, 4, 4)),
+    (C48, 97, 4100, 2176, (4, 4, 4)), (C48, 300, 1000, 416, (2, 4, 8)),
+])
+def test_small_m_configuration(plan, form, M, N, K, cfg):
+    out = (ctypes.c_int * 4)()
+    plan.plan_skinny(M, N, K, form, 256, out)
+    assert tuple(out) == (1, *cfg)
