@@ -1917,7 +1917,6 @@ __global__ __launch_bounds__(256) void k_linear_slots_nv(SlotBuf p1, SlotBuf p2,
 }
 
 // The small-M kernel of the formats on 16-bit MFMA (sharq_skinny16.hip).
-bool use_skinny16(bool nv, int64_t M, int N, int K);
 hipError_t launch_linear_skinny16(bool nv, int pat, int ydt, const uint8_t* spc, const uint8_t* spm,
                                   const uint8_t* sps, const uint8_t* dnc, const uint8_t* dns, const float* tsx,
                                   int64_t M, const uint8_t* wc, const uint8_t* ws, const float* tsw, int N, int K,
@@ -2347,7 +2346,7 @@ hipError_t launch_linear_slots(int mode, int pat, int ydt, bool nv, const uint8_
 hipError_t launch_linear_hif4(int ydt, const uint8_t* spc, const uint8_t* spm, const uint8_t* sps, const uint8_t* dnc,
                               const uint8_t* dns, int64_t M, const uint8_t* wc, const uint8_t* ws, int N, int K,
                               void* Y, int64_t ldy, hipStream_t st) {
-  if (use_skinny16(false, M, N, K))
+  if (use_skinny16(M, N, K, form16(false, 24), device_cus()))
     return launch_linear_skinny16(false, 24, ydt, spc, spm, sps, dnc, dns, nullptr, M, wc, ws, nullptr, N, K, Y, ldy,
                                   st);
   if (K % kBK == 0) return launch_linear16_hif4(ydt, spc, spm, sps, dnc, dns, M, wc, ws, N, K, Y, ldy, st);

@@ -14,7 +14,6 @@
 namespace sharq {
 
 // The small-M kernel of the formats on 16-bit MFMA (sharq_skinny16.hip).
-bool use_skinny16(bool nv, int64_t M, int N, int K);
 hipError_t launch_linear_skinny16(bool nv, int pat, int ydt, const uint8_t* spc, const uint8_t* spm,
                                   const uint8_t* sps, const uint8_t* dnc, const uint8_t* dns, const float* tsx,
                                   int64_t M, const uint8_t* wc, const uint8_t* ws, const float* tsw, int N, int K,
@@ -567,7 +566,7 @@ __global__ __launch_bounds__(kT16) void k_linear16(Args16 p, OutT* Y, int64_t ld
 
 template <int FMT, int PAT, typename OutT>
 static hipError_t go_linear16(const Args16& a, void* Y, int64_t ldy, hipStream_t st) {
-  const Plan16 p = plan16(a.M, a.N, device_cus());
+  const Plan16 p = plan16(a.M, a.N, form16(FMT == kFmtNv, PAT), device_cus());
   OutT* y = reinterpret_cast<OutT*>(Y);
   const dim3 grid((unsigned)p.grid), block(kT16);
   if (p.nf == 4) k_linear16<FMT, PAT, OutT, 4><<<grid, block, 0, st>>>(a, y, ldy, p.gx, p.gy, p.full);
@@ -607,7 +606,7 @@ hipError_t launch_linear_nv(int pat, int ydt, const uint8_t* spc, const uint8_t*
                             const uint8_t* ws, const float* tsw, int N, int K, void* Y, int64_t ldy,
                             const uint8_t* spd, hipStream_t st) {
   const bool dense = spd && K % kBK == 0;
-  if ((dense || spc != nullptr) && use_skinny16(true, M, N, K))
+  if ((dense || spc != nullptr) && use_skinny16(M, N, K, form16(true, dense ? 0 : pat), device_cus()))
     return launch_linear_skinny16(true, dense ? 0 : pat, ydt, dense ? spd : spc, spm, sps, dnc, dns, tsx, M, wc, ws,
                                   tsw, N, K, Y, ldy, st);
   if (dense) return go_nv_dt<0>(ydt, spd, nullptr, sps, dnc, dns, tsx, M, wc, ws, tsw, N, K, Y, ldy, st);

@@ -136,35 +136,100 @@ constexpr bool use_skinny(int64_t M, int N, int K, int form, int main_form, int 
 
 constexpr int kRows16 = 256;   // rows of a tile
 
-// Tile width and whole tiles of a launch.  A tile of 64 NF columns takes about
-// (NF + 1) / 5 of a 256-column one (its activation work does not shrink with
-// it; NVFP4 0.63, 0.93 and 1.10 us a step for NF 2, 3 and 4), and the launch as long as its rounds of tiles over the CUs: the
-// cheapest width wins, the wider of equals.  A last round of 256-column tiles
-// that is at most half full runs as half tiles.
+// By format and backbone: NVFP4 dense copy, NVFP4 2:4 and 4:8 compressed, HiF4 2:4.
+constexpr int form16(bool nv, int pat) { return nv ? backbone_form(pat) : 3; }
+
+// Tile width and whole tiles of a launch.  The launch takes as long as its
+// rounds of tiles over the CUs; the cheapest width wins, the wider of equals.  A
+// last round of 256-column tiles that is at most half full runs as half tiles.
+// us: the estimate per 32 positions, from a tile's measured step by NF (4, 3, 2)
+// and form; a narrower tile's activation work does not shrink with it.
 struct Plan16 {
   int nf, gx, gy, full, grid;
-  int64_t cost;   // in fifths of a whole 256-column tile
+  double us;
 };
 
-constexpr Plan16 plan16(int64_t M, int N, int cus) {
+constexpr Plan16 plan16(int64_t M, int N, int form, int cus) {
+  constexpr double kStep[4][3] = {{1.16, 0.93, 0.64}, {1.43, 1.08, 0.75}, {1.62, 1.25, 0.99}, {1.81, 1.48, 1.13}};
   const int gy = (int)((M + kRows16 - 1) / kRows16);
   Plan16 best{};
-  int64_t least = 0;
   for (int nf = 4; nf >= 2; --nf) {
-    const int gx = (N + 64 * nf - 1) / (64 * nf);
+    const int gx = (int)(((int64_t)N + 64 * nf - 1) / (64 * nf));
     const int64_t tiles = (int64_t)gx * gy, r = tiles % cus;
-    int64_t cost = (tiles + cus - 1) / cus * (nf + 1);
-    Plan16 p{nf, gx, gy, (int)tiles, (int)(tiles < cus ? tiles : cus), 0};
+    Plan16 p{nf, gx, gy, (int)tiles, (int)(tiles < cus ? tiles : cus), 0.0};
+    p.us = (double)((tiles + cus - 1) / cus) * kStep[form][4 - nf];
     if (nf == 4 && tiles > cus && r > 0 && 2 * r <= cus) {
       p.full = (int)(tiles - r);
-      cost = tiles / cus * 5 + 3;
+      p.us = (double)(tiles / cus) * kStep[form][0] + kStep[form][2];
     }
-    if (least == 0 || cost < least) {
-      best = p;
-      best.cost = least = cost;
-    }
+    if (best.nf == 0 || p.us < best.us) best = p;
   }
   return best;
+}
+
+// ---------------------------------------------------------------------------
+// NVFP4 and HiF4 with few rows (k_linear_skinny16)
+// ---------------------------------------------------------------------------
+
+// Above 32 rows: 16 mf rows and 16 nb columns to a workgroup, K over ks
+// wavefronts.  A launch takes us[0] + us[1] (R - 1) + (us[2] R + us[3] R2) panels
+// / 32, R and R2 the rounds of workgroups and of pairs of them over the CUs (two
+// of some fit a CU), by form; the last three rows: 2:4, 4:8 and HiF4 with K not a
+// multiple of 128.  Fitted to 379 and 120 shapes per form with the weight
+// streamed from HBM (N 512 to 37888, K 768 to 18944, M 33 to 4096; nine in ten
+// within 4 to 10%).  With one figure for every NVFP4 form in their place, 2:4 and
+// 4:8 calls ran up to 1.8 times as long here as on the prefill kernel (M 640 N
+// 6144 K 4096 4:8: 198 us, there 117).
+struct Cfg16 {
+  int mf, nb, ks;
+  double us[7][4];
+};
+constexpr double kNotBuilt = 1e9;   // never the least for these forms
+constexpr Cfg16 kCfg16[4] = {
+    {2, 1, 8, {{3.11, 0.35, 4.42}, {3.26, 0.18, 6.34}, {3.34, 0.16, 9.94}, {3.06, 1.02, 14.2},
+               {3.70, 0.24, 5.86, 1.97}, {3.95, 0.10, 9.47, 2.48}, {3.46, 1.20, 17.5}}},
+    {2, 2, 8, {{3.27, 1.43, 6.17}, {3.34, 1.33, 8.07}, {3.44, 1.32, 11.8}, {3.38, 1.38, 16.7},
+               {3.69, 1.46, 9.90}, {3.80, 1.50, 14.4}, {4.06, 1.78, 20.2}}},
+    {2, 4, 4, {{4.69, 1.07, 5.69, 5.88}, {4.95, 1.05, 7.43, 4.95}, {4.79, 2.76, 15.5}, {5.18, 2.96, 23.0},
+               {6.11, 1.17, 9.06, 2.85}, {6.54, 1.27, 12.5, 2.37}, {6.60, 4.28, 24.4}}},
+    {4, 4, 4, {{kNotBuilt}, {kNotBuilt}, {6.96, 4.68, 27.1}, {7.37, 4.88, 37.1},
+               {kNotBuilt}, {9.07, 6.50, 27.3}, {9.86, 7.15, 37.1}}},
+};
+
+struct Wide16 {
+  int mf, nb, ks;
+  double us;
+};
+
+constexpr Wide16 wide16(int64_t M, int N, int K, int form, int cus) {
+  const double panels = (double)((K + 127) / 128) / 32.0;
+  Wide16 best{};
+  for (const Cfg16& c : kCfg16) {
+    const double(&t)[4] = c.us[K % 128 == 0 ? form : form + 3];   // the dense copy needs K a multiple of 128
+    const int64_t wgs = ((int64_t)N + 16 * c.nb - 1) / (16 * c.nb) * ((M + 16 * c.mf - 1) / (16 * c.mf));
+    const double r = (double)((wgs + cus - 1) / cus), r2 = (double)((wgs + 2 * cus - 1) / (2 * cus));
+    const double us = t[0] + t[1] * (r - 1.0) + (t[2] * r + t[3] * r2) * panels;
+    if (best.mf == 0 || us < best.us) best = {c.mf, c.nb, c.ks, us};
+  }
+  return best;
+}
+
+// Up to 32 rows always (the layer streams its weight); above, where the
+// estimate is below the prefill kernel's: a start and its plan's time per 32
+// positions, or, K not a multiple of 128, the simpler kernels' rounds of 128 x
+// 256 tiles (same shapes; nine in ten within 3 to 9%).
+constexpr bool use_skinny16(int64_t M, int N, int K, int form, int cus) {
+  constexpr double kStart[4] = {6.0, 6.6, 7.2, 6.2}, kRagged[4] = {1.41, 1.23, 1.41, 1.90};
+  if (M <= 32) return true;
+  if (M > 4096) return false;
+  double main_us = 0.0;
+  if (K % 128 == 0) {
+    main_us = kStart[form] + plan16(M, N, form, cus).us * K / 32.0;
+  } else {
+    const int64_t tiles = ((M + 127) / 128) * (((int64_t)N + 255) / 256);
+    main_us = 9.6 + (double)((tiles + cus - 1) / cus) * kRagged[form] * K / 32.0;
+  }
+  return wide16(M, N, K, form, cus).us < main_us;
 }
 
 }  // namespace sharq

@@ -218,56 +218,31 @@ static hipError_t go_s16(const Skinny16Args& p, const float* tsx, const float* t
   return hipGetLastError();
 }
 
-// (row fragments, column fragments, K splits).  Column fragments: as many as
-// leave at least 192 workgroups, since every activation block loaded and
-// dequantized then feeds more weight columns; up to 16 rows the K split of the
-// MXFP4 kernel (about 8192 weight streams in flight, at least 4 panels per
+// (row fragments, column fragments, K splits).  Up to 32 rows, column fragments:
+// as many as leave at least 192 workgroups, since every activation block loaded
+// and dequantized then feeds more weight columns; up to 16 rows the K split of
+// the MXFP4 kernel (about 8192 weight streams in flight, at least 4 panels per
 // wavefront).  Measured with the weight streamed from HBM, us for (N, K) =
-// (6144, 4096) / (28672, 4096) / (4096, 14336) / (1024, 4096):
-//   NVFP4 M = 16   (1,1,16) 8.0/28.7/11.2/4.6  (1,2,8) 6.2/19.1/15.5/5.6  (1,4,4) 11.4/17.9/29.9/10.7
-//   NVFP4 M = 64   (2,1,8) 15.3/61.3/30.5/6.8  (2,2,8) 15.3/54.4/22.3/8.0  (2,4,4) 15.6/41.6/41.2/15.4
-//   NVFP4 M = 256  (4,1,8) 61.9/291/115/11.3   (4,2,4) 34.8/147/69.7/16.0 (2,4,4) 32.0/130/64.9/15.4
-//   HiF4  M = 256  (4,1,8) 153/724/339/26.7    (4,2,4) 101/473/208/34.3   (4,4,4) 84.0/298/133/43.5
-// where the 128 x 256 prefill tile took 92/109/298/89 (NVFP4) and
-// 252/254/854/247 (HiF4) at every M up to 256.
+// (6144, 4096) / (28672, 4096) / (4096, 14336) / (1024, 4096), M = 16, NVFP4:
+// (1,1,16) 8.0/28.7/11.2/4.6, (1,2,8) 6.2/19.1/15.5/5.6, (1,4,4) 11.4/17.9/29.9/10.7,
+// where the 128 x 256 prefill tile took 92/109/298/89.
 struct S16Cfg {
   int mf, nb, ks;
 };
 
-static S16Cfg s16_config(bool nv, int64_t M, int N, int K) {
-  const int mf = M <= 16 ? 1 : M <= (nv ? 256 : 128) ? 2 : 4;
-  const int64_t nrt = (M + 16 * mf - 1) / (16 * mf);
-  int nb = nv && mf == 4 ? 2 : 4;
-  while (nb > 1 && (N + 16 * nb - 1) / (16 * nb) * nrt < 192) nb >>= 1;
-  if (mf > 1) return {mf, nb, nb == 4 || (mf == 4 && nb == 2) ? 4 : 8};
+static S16Cfg s16_config(int form, int64_t M, int N, int K) {
+  if (M > 32) {
+    const Wide16 w = wide16(M, N, K, form, device_cus());
+    return {w.mf, w.nb, w.ks};
+  }
+  const int mf = M <= 16 ? 1 : 2;
+  int nb = 4;
+  while (nb > 1 && (N + 16 * nb - 1) / (16 * nb) < 192) nb >>= 1;
+  if (mf > 1) return {mf, nb, nb == 4 ? 4 : 8};
   const int nks = (K + 127) / 128, cap = nb == 4 ? 8 : 16, streams = (N + 15) / 16;
   int ks = 4;
   while (ks < cap && streams * ks * 2 <= 8192 && nks >= 4 * ks * 2) ks *= 2;
   return {mf, nb, ks};
-}
-
-// Up to 32 rows always (the layer streams its weight); above, where the
-// estimate of this kernel's time is below the prefill kernel's.  This
-// kernel's grows with the padded work, 5 (NVFP4) or 11 (HiF4) us per 1e9 M N
-// K; the prefill kernel's with its plan's rounds and K, 0.21 or 0.38 us per
-// unit of tile cost and 32 positions (K not a multiple of 128: the simpler
-// kernels, 0.69 or 1.93 us per round of 128 x 256 tiles).  Measured, this
-// kernel / prefill kernel, us: NVFP4 N 6144 K 4096 M 512 63 / 83, M 768 93 / 84;
-// N 28672 K 4096 M 96 59 / 88, M 256 130 / 92; N 12288 K 1024 M 256 21 / 25, M
-// 400 38 / 26; N 2048 K 2048 M 1536 36 / 44.  HiF4 N 6144 K 4096 M 512 126 / 149, M
-// 768 208 / 152; N 28672 K 4096 M 48 89 / 151, M 160 235 / 157.
-bool use_skinny16(bool nv, int64_t M, int N, int K) {
-  if (M <= 32) return true;
-  if (M > 4096) return false;
-  const int64_t rows = (M + 15) / 16 * 16, cols = (N + 15) / 16 * 16;
-  double main_us;   // per 32 positions
-  if (K % 128 == 0) {
-    main_us = (double)plan16(M, N, device_cus()).cost * (nv ? 0.21 : 0.38);
-  } else {
-    const int64_t tiles = ((M + 127) / 128) * ((int64_t)(N + 255) / 256), cus = device_cus();
-    main_us = (double)((tiles + cus - 1) / cus) * (nv ? 0.69 : 1.93);
-  }
-  return (double)rows * (double)cols * (nv ? 5.0e-9 : 1.1e-8) < main_us / 32.0;
 }
 
 template <int FMT, int PAT>
@@ -279,8 +254,7 @@ static hipError_t go_s16_cfg(const Skinny16Args& p, const float* tsx, const floa
   SHARQ_S16(1, 2, 4) SHARQ_S16(1, 2, 8) SHARQ_S16(1, 2, 16)
   SHARQ_S16(1, 4, 4) SHARQ_S16(1, 4, 8)
   SHARQ_S16(2, 1, 8) SHARQ_S16(2, 2, 8) SHARQ_S16(2, 4, 4)
-  SHARQ_S16(4, 1, 8) SHARQ_S16(4, 2, 4)
-  if constexpr (FMT == kFmtHf) { SHARQ_S16(4, 4, 4) }
+  if constexpr (FMT == kFmtHf || PAT == 48) { SHARQ_S16(4, 4, 4) }
 #undef SHARQ_S16
   return hipErrorInvalidValue;   // unreachable: s16_config gives one of the above
 }
@@ -290,7 +264,7 @@ hipError_t launch_linear_skinny16(bool nv, int pat, int ydt, const uint8_t* spc,
                                   int64_t M, const uint8_t* wc, const uint8_t* ws, const float* tsw, int N, int K,
                                   void* Y, int64_t ldy, hipStream_t st) {
   const Skinny16Args p{spc, spm, sps, dnc, dns, wc, ws, M, N, K};
-  const S16Cfg c = s16_config(nv, M, N, K);
+  const S16Cfg c = s16_config(form16(nv, pat), M, N, K);
   if (!nv) return go_s16_cfg<kFmtHf, 24>(p, tsx, tsw, Y, ydt, ldy, st, c);
   if (pat == 0) return go_s16_cfg<kFmtNv, 0>(p, tsx, tsw, Y, ydt, ldy, st, c);
   if (pat == 24) return go_s16_cfg<kFmtNv, 24>(p, tsx, tsw, Y, ydt, ldy, st, c);

@@ -50,7 +50,7 @@ def check(S, G, o, wo, dense, T, N, K, dtypes=(torch.float32, torch.bfloat16)):
     (2100, 1992),    # 256 x 128 tiles, ragged in both
     (2040, 6104),    # 256 x 192 tiles
     (2290, 7101),    # 256 x 256 tiles, rows of odd length
-    (2300, 8008),    # 256 x 256 tiles and a last round of half tiles
+    (2300, 8008),    # 256 x 256 tiles and a last round of half tiles (NVFP4 compressed: 256 x 192)
 ])
 @pytest.mark.parametrize("fmt,n,m,dense,K", [("nv", 2, 4, True, 256), ("nv", 2, 4, False, 128),
                                              ("nv", 4, 8, False, 384), ("hif4", 2, 4, False, 256)])
@@ -58,6 +58,14 @@ def test_linear16(S, G, fmt, n, m, dense, K, T, N):
     x = synth.activations(T, K, seed=T + N)
     o = O.prepare(x, synth.gamma(K, seed=3), 1e-6, n, m, fmt)
     check(S, G, o, O.quantize_weight(synth.weight(N, K, seed=7), fmt), dense, T, N, K)
+
+
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
+def test_linear16_half_tiles_compressed(S, G, n, m):
+    """792 tiles of 256 x 256 on 256 CUs: three rounds and one of half tiles."""
+    T, N, K = 2300, 22400, 128
+    o = O.prepare(synth.activations(T, K, seed=1), synth.gamma(K, seed=3), 1e-6, n, m, "nv")
+    check(S, G, o, O.quantize_weight(synth.weight(N, K, seed=7), "nv"), False, T, N, K, (torch.float32,))
 
 
 def test_nv_scales_around_the_merge_rule(S, G):

@@ -51,13 +51,22 @@ def check(S, G, fmt, T, N, K, n, m, dense):
     (1, 1, 64), (3, 17, 128), (16, 31, 192), (5, 3100, 320),      # one row fragment; 1, 2 and 4 column fragments
     (2, 12300, 128), (1, 48, 8192), (1, 6150, 4096),               # K splits of 4, 8 and 16
     (17, 33, 64), (33, 65, 1216), (128, 300, 448), (40, 6200, 256),   # two row fragments, several row tiles
-    (129, 70, 192), (200, 1000, 576), (257, 500, 128),             # four row fragments
+    (129, 70, 192), (200, 1000, 576), (257, 500, 128),             # one row past a tile
 ])
 @pytest.mark.parametrize("fmt,n,m,dense", [("nv", 2, 4, False), ("nv", 4, 8, False), ("nv", 4, 8, True),
                                            ("hif4", 2, 4, False)])
 def test_skinny16(S, G, fmt, n, m, dense, T, N, K):
     if dense and K % 128:
         pytest.skip("the dense backbone copy needs K a multiple of 128")
+    check(S, G, fmt, T, N, K, n, m, dense)
+
+
+@pytest.mark.parametrize("fmt,T,N,K,n,m,dense", [
+    ("nv", 97, 6200, 256, 4, 8, True), ("nv", 300, 3000, 256, 2, 4, False), ("nv", 100, 4100, 576, 4, 8, False),   # 32 x 64
+    ("nv", 300, 3000, 256, 4, 8, False), ("hif4", 97, 6200, 256, 2, 4, False), ("hif4", 100, 4100, 448, 2, 4, False),   # 64 x 64
+])
+def test_row_tiles(S, G, fmt, T, N, K, n, m, dense):
+    """The wider configurations above 32 rows, with a last row tile of one row or more and ragged columns."""
     check(S, G, fmt, T, N, K, n, m, dense)
 
 

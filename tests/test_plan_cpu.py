@@ -17,18 +17,22 @@ SHIM = r"""
 using namespace sharq;
 extern "C" {
 // {nf, gx, gy, full, grid} of the plan
-void plan_mx8(int64_t M, int N, int cus, int* out) {
+void plan_mx8(int64_t M, int N, int cus, int* out, int) {
   const Plan8 p = plan8(M, N, cus);
   out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid;
 }
-void plan_16(int64_t M, int N, int cus, int* out) {
-  const Plan16 p = plan16(M, N, cus);
+void plan_16(int64_t M, int N, int cus, int* out, int form) {
+  const Plan16 p = plan16(M, N, form, cus);
   out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid;
 }
 // {small-M kernel or not, mf, nb, ks of its configuration above 32 rows}
 void plan_skinny(int64_t M, int N, int K, int form, int cus, int* out) {
   const SkinnyWide w = skinny_wide(M, N, K, form, cus);
   out[0] = use_skinny(M, N, K, form, form, cus), out[1] = w.mf, out[2] = w.nb, out[3] = w.ks;
+}
+void plan_skinny16(int64_t M, int N, int K, int form, int cus, int* out) {
+  const Wide16 w = wide16(M, N, K, form, cus);
+  out[0] = use_skinny16(M, N, K, form, cus), out[1] = w.mf, out[2] = w.nb, out[3] = w.ks;
 }
 // row and column tile of every id in [0, units)
 void walk(int units, int gx, int gy, int* mt, int* nt) {
@@ -47,8 +51,9 @@ def plan(tmp_path_factory):
                     os.path.join(ROOT, "paper_2606_26587_amd", "csrc"), str(d / "shim.cpp"), "-o", so], check=True)
     L = ctypes.CDLL(so)
     for f in (L.plan_mx8, L.plan_16):
-        f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
-    L.plan_skinny.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
+        f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.c_int]
+    for f in (L.plan_skinny, L.plan_skinny16):
+        f.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     return L
 
 
@@ -66,13 +71,13 @@ def rounds_of(L, units, gx, gy, grid):
     return int(np.bincount(np.arange(units) % grid, minlength=grid).max())
 
 
-@pytest.mark.parametrize("name", ["plan_mx8", "plan_16"])
+@pytest.mark.parametrize("name,form", [("plan_mx8", 0)] + [("plan_16", f) for f in range(4)])
 @pytest.mark.parametrize("cus", [256, 64, 38])
-def test_rounds(plan, name, cus):
+def test_rounds(plan, name, form, cus):
     out = (ctypes.c_int * 5)()
     odd = 0
     for M, N in SIZES:
-        getattr(plan, name)(M, N, cus, out)
+        getattr(plan, name)(M, N, cus, out, form)
         nf, gx, gy, full, grid = out
         assert gx == -(-N // (64 * nf)) and gy == -(-M // 256)
         odd += full % 8 != 0
@@ -80,6 +85,18 @@ def test_rounds(plan, name, cus):
         rest = gx * gy - full   # a last round of half tiles
         assert rest == 0 or (nf == 4 and full % cus == 0 and 2 * rest <= grid)
     assert odd > 20   # tile counts that are no multiple of 8 are among them
+
+
+@pytest.mark.parametrize("form,M,N,nf,halves", [
+    # the tile widths that tests/test_gpu_linear16.py runs (forms: NVFP4 dense, 2:4, 4:8, HiF4)
+    *[(f, 2100, 1992, 2, False) for f in range(4)], *[(f, 2040, 6104, 3, False) for f in range(4)],
+    *[(f, 2290, 7101, 4, False) for f in range(4)], (0, 2300, 8008, 4, True), (3, 2300, 8008, 4, True),
+    (1, 2300, 22400, 4, True), (2, 2300, 22400, 4, True),
+])
+def test_tile_widths(plan, form, M, N, nf, halves):
+    out = (ctypes.c_int * 5)()
+    plan.plan_16(M, N, 256, out, form)
+    assert out[0] == nf and (out[3] < out[1] * out[2]) == halves
 
 
 DENSE, C24, C48 = 0, 1, 2
@@ -117,3 +134,47 @@ def test_small_m_configuration(plan, form, M, N, K, cfg):
     out = (ctypes.c_int * 4)()
     plan.plan_skinny(M, N, K, form, 256, out)
     assert tuple(out) == (1, *cfg)
+
+
+NV_DENSE, NV24, NV48, HIF4 = 0, 1, 2, 3
+
+
+@pytest.mark.parametrize("form,M,N,K,small", [
+    # (us on one card, the weight streamed: small-M kernel / prefill kernel)
+    (NV48, 1024, 6144, 4096, False),
+    (NV24, 1792, 2048, 768, False),      # 42 / 26
+    (NV48, 1792, 2048, 768, False),      # 54 / 29
+    (NV48, 2560, 2048, 768, False),
+    (NV48, 768, 5000, 2080, True),       # 71 with 32 x 64 columns / 104, K not a multiple of 128
+    (NV_DENSE, 256, 6144, 4096, True),   # 32 / 75
+    (NV48, 128, 4096, 4096, True), (HIF4, 96, 4096, 4096, True), (NV24, 64, 28672, 4096, True),
+    (NV_DENSE, 32, 37888, 3584, True), (HIF4, 1, 64, 64, True), (NV24, 4097, 64, 128, False),
+])
+def test_small_m_choice_16_bit(plan, form, M, N, K, small):
+    out = (ctypes.c_int * 4)()
+    plan.plan_skinny16(M, N, K, form, 256, out)
+    assert bool(out[0]) == small, (M, N, K)
+
+
+@pytest.mark.parametrize("form,M,N,K,cfg", [
+    # what tests/test_gpu_skinny16.py::test_row_tiles runs
+    (NV_DENSE, 97, 6200, 256, (2, 4, 4)), (NV24, 300, 3000, 256, (2, 4, 4)), (NV48, 100, 4100, 576, (2, 4, 4)),
+    (NV48, 300, 3000, 256, (4, 4, 4)), (HIF4, 97, 6200, 256, (4, 4, 4)), (HIF4, 100, 4100, 448, (4, 4, 4)),
+    (NV_DENSE, 257, 500, 128, (2, 2, 8)), (NV24, 128, 300, 448, (2, 1, 8)),
+])
+def test_small_m_configuration_16_bit(plan, form, M, N, K, cfg):
+    out = (ctypes.c_int * 4)()
+    plan.plan_skinny16(M, N, K, form, 256, out)
+    assert tuple(out) == (1, *cfg)
+
+
+def test_small_m_configurations_are_built(plan):
+    """Over 32 rows no form is given a configuration that it is not built for (64 x 64: NVFP4 4:8 and HiF4)."""
+    out = (ctypes.c_int * 4)()
+    for form in range(4):
+        for M in (33, 64, 128, 257, 1000, 4096):
+            for N in (1, 100, 1000, 4100, 12000, 50000, 1 << 20):
+                for K in (128, 4096, 16384) if form == NV_DENSE else (64, 128, 576, 4096, 16384):
+                    plan.plan_skinny16(M, N, K, form, 256, out)
+                    assert tuple(out)[1:] in {(2, 1, 8), (2, 2, 8), (2, 4, 4), (4, 4, 4)}
+                    assert form >= 2 or out[1] == 2
