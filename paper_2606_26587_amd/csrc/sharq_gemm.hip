@@ -1457,7 +1457,10 @@ __global__ __launch_bounds__(64 * KS) void k_linear_mx_skinny(SkinnyArgs p, void
 // further slots, the first of the grid, which find theirs by a scan (most end
 // there): walking them in one workgroup took 55 us instead of 7.6 where all 512
 // rows have one expert of 128 (N 2048, K 768).  extra >= the sum over experts
-// of (rows - 1) / CH.
+// of (rows - 1) / CH.  K is split over KS wavefronts: where routing leaves few
+// workgroups with rows, their loads in flight bound the launch (without a split
+// E 8, N 28672, K 4096, 64 rows of one expert 41.0 us, 18.3 with 8 rows; E 128, N
+// 1536, K 2048, 128 rows 35.9, 28.6 split in four).
 template <int CH>
 __device__ __forceinline__ bool grouped_chunk(const int32_t* offs, int E, int extra, int slot, int& e, int& lo,
                                               int& hi) {
@@ -1496,7 +1499,6 @@ __device__ __forceinline__ bool grouped_chunk(const int32_t* offs, int E, int ex
   return hi > lo;
 }
 
-// K split over the KS wavefronts, for column groups that do not fill the chip.
 template <int MF, int NB, int KS, int PAT, bool RAG>
 __global__ __launch_bounds__(64 * KS) void k_linear_mx_grouped_skinny(SkinnyArgs p, const int32_t* ridx,
                                                                       const int32_t* offs, int E, int extra, void* Y,
@@ -1516,50 +1518,6 @@ __global__ __launch_bounds__(64 * KS) void k_linear_mx_grouped_skinny(SkinnyArgs
     row[m] = ridx ? (int64_t)ridx[i] : (int64_t)i;
   }
   skinny_compute<MF, NB, KS, PAT, RAG>(p, row, lo, hi, cg * 16 * NB, Y, ydt, ldy, part);
-}
-
-// For many column groups: one wavefront each, without splitting K.  Two row
-// tiles per wavefront (MF 2) cost occupancy and measured 33 us against 24 at
-// E 128, N 2048, K 768, 4 rows a mean; 32 columns 27, 128 columns 26.
-template <int NB, int PAT, bool RAG>
-__global__ __launch_bounds__(64) void k_linear_mx_grouped_rows(SkinnyArgs p, const int32_t* ridx, const int32_t* offs,
-                                                               int E, int extra, void* Y, int ydt, int64_t ldy,
-                                                               int ncg) {
-  const int lane = threadIdx.x;
-  const int slot = (int)blockIdx.x / ncg, cg = (int)blockIdx.x - slot * ncg, n0 = cg * 16 * NB;
-  int e, lo, hi;
-  if (!grouped_chunk<16>(offs, E, extra, slot, e, lo, hi)) return;
-  p.wc += (int64_t)e * p.N * (p.K / 2);
-  p.ws += (int64_t)e * p.N * (p.K / 32);
-  const int nks = (p.K + kBK - 1) / kBK;
-  const int i = lo + (lane & 15), ic = i < hi ? i : hi - 1;   // loads stay in bounds, stores are masked
-  const int64_t row[1] = {ridx ? (int64_t)ridx[ic] : (int64_t)ic};
-  v4f_t acc[1][NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) acc[0][n] = v4f_t{0.0f, 0.0f, 0.0f, 0.0f};
-  SkinnyStage<1, NB> s0, s1;
-  skinny_load<1, NB, PAT, RAG>(s0, p, row, n0, 0, lane);
-  if (nks > 1) skinny_load<1, NB, PAT, RAG>(s1, p, row, n0, 1, lane);
-  int ks = 0;
-  for (; ks + 1 < nks; ks += 2) {
-    skinny_step<1, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
-    if (ks + 2 < nks) skinny_load<1, NB, PAT, RAG>(s0, p, row, n0, ks + 2, lane);
-    skinny_step<1, NB, PAT, RAG>(acc, s1, p.K, ks + 1, lane);
-    if (ks + 3 < nks) skinny_load<1, NB, PAT, RAG>(s1, p, row, n0, ks + 3, lane);
-  }
-  if (ks < nks) skinny_step<1, NB, PAT, RAG>(acc, s0, p.K, ks, lane);
-  if (i >= hi) return;
-#pragma unroll
-  for (int n = 0; n < NB; ++n)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int col = n0 + 16 * n + 4 * (lane >> 4) + r;
-      if (col >= p.N) continue;
-      const int64_t at = (int64_t)i * ldy + col;
-      if (ydt == 2) reinterpret_cast<float*>(Y)[at] = acc[0][n][r];
-      else if (ydt == 1) reinterpret_cast<_Float16*>(Y)[at] = (_Float16)acc[0][n][r];
-      else reinterpret_cast<uint16_t*>(Y)[at] = f32_to_bf16_rne(acc[0][n][r]);
-    }
 }
 
 template <int MF, int NB, int KS, int PAT>
@@ -2181,44 +2139,13 @@ static hipError_t go_grouped_skinny(const SkinnyArgs& p, const int32_t* ridx, co
   return hipGetLastError();
 }
 
-template <int NB, int PAT>
-static hipError_t go_grouped_rows(const SkinnyArgs& p, const int32_t* ridx, const int32_t* offs, int E, int64_t total,
-                                  void* Y, int ydt, int64_t ldy, hipStream_t st) {
-  const int ncg = (p.N + 16 * NB - 1) / (16 * NB);
-  const int extra = (int)(total / 16);
-  const dim3 grid((unsigned)ncg * (unsigned)(E + extra)), block(64);
-  if constexpr (PAT != 0) {
-    if (p.K % kBK != 0) {
-      k_linear_mx_grouped_rows<NB, PAT, true><<<grid, block, 0, st>>>(p, ridx, offs, E, extra, Y, ydt, ldy, ncg);
-      return hipGetLastError();
-    }
-  }
-  k_linear_mx_grouped_rows<NB, PAT, false><<<grid, block, 0, st>>>(p, ridx, offs, E, extra, Y, ydt, ldy, ncg);
-  return hipGetLastError();
-}
-
-// Few rows per expert: by the number of 64-column groups over all experts
-// (many fill the chip without splitting K) and the mean rows of an expert (the
-// host does not know the routing).  Measured, these kernels / the persistent
-// one (us, weights streamed, random routing): E 128 N 2048 K 768, mean 4 rows
-// 24 / 41, 16 41 / 43; E 128 N 1536 K 2048, 4 47 / 62, 16 67 / 65; E 32 N 2048 K 2048,
-// 8 19 / 24, 16 21 / 23; E 8 N 2048 K 4096, 8 9.2 / 24.8, 24 12.6 / 24.9, 32 19.6 /
-// 24.9.  At most 512 rows: where few experts have all of them, the persistent
-// kernel's 128-row tiles re-read less (E 128 N 1536 K 2048, 8 experts: 512 rows 12.4
-// / 11.7, 1024 19.5 / 12.2).
-static bool grouped_many(int E, int N) { return (int64_t)E * ((N + 63) / 64) >= 768; }
-
-static bool use_grouped_skinny(int64_t total, int E, int N) {
-  if (((int64_t)E + 32) * ((N + 31) / 32) > (1 << 30)) return false;   // the grid
-  return total <= 512 && total <= (grouped_many(E, N) ? 8 : 24) * (int64_t)E;
-}
-
 template <int PAT>
 static hipError_t go_grouped_skinny_cfg(const SkinnyArgs& p, const int32_t* ridx, const int32_t* offs, int E,
                                         int64_t total, void* Y, int ydt, int64_t ldy, hipStream_t st) {
-  if (grouped_many(E, p.N)) return go_grouped_rows<4, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
-  if (total > 8 * (int64_t)E) return go_grouped_skinny<2, 4, 4, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
-  return go_grouped_skinny<1, 2, 4, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
+  const GroupedCfg c = grouped_cfg(total, E, p.N, p.K, device_cus());
+  if (c.nb == 2) return go_grouped_skinny<1, 2, 4, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
+  if (c.ks == 2) return go_grouped_skinny<1, 4, 2, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
+  return go_grouped_skinny<1, 4, 4, PAT>(p, ridx, offs, E, total, Y, ydt, ldy, st);
 }
 
 template <int NF, int PAT, bool SDW, typename OutT>
@@ -2274,7 +2201,7 @@ hipError_t launch_linear_mx_grouped(int pat, int ydt, const uint8_t* spc, const 
   // interleaved pipeline's loads need
   const bool sdw = K >= kBK && ((int64_t)N * (K / 32)) % 4 == 0;
   constexpr int NF = 8;
-  if (use_grouped_skinny(total, E, N)) {
+  if (use_grouped_skinny(total, E, N, device_cus())) {
     if (spd && K % kBK == 0)
       return go_grouped_skinny_cfg<0>(SkinnyArgs{spd, nullptr, sps, dnc, dns, wc, ws, act_rows, N, K}, ridx, offs, E,
                                       total, Y, ydt, ldy, st);

@@ -131,6 +131,39 @@ constexpr bool use_skinny(int64_t M, int N, int K, int form, int main_form, int 
 }
 
 // ---------------------------------------------------------------------------
+// MXFP4, grouped, with few rows (k_linear_mx_grouped_skinny)
+// ---------------------------------------------------------------------------
+
+// 16 rows and 16 nb columns of an expert to a workgroup, K over ks wavefronts.
+// 32 columns where a few experts leave the chip idle with 64; K in two parts
+// where it has less than 12 panels.  E 128 N 2048 K 768, 512 rows: 24.8 us with 2
+// parts, 30.6 with 4; N 1536 K 2048, 256 rows: 35.8, 35.0; E 8 N 2048 K 4096, 64 rows:
+// 10.0 with 32 columns, 11.3 with 64.
+struct GroupedCfg {
+  int nb, ks;
+};
+constexpr GroupedCfg grouped_cfg(int64_t total, int E, int N, int K, int cus) {
+  const int64_t groups = (int64_t)E * (((int64_t)N + 63) / 64);
+  if ((groups <= 2 * cus && total <= E) || (groups <= cus && total <= 8 * (int64_t)E)) return {2, 4};
+  return {4, (K + 127) / 128 >= 12 ? 4 : 2};
+}
+
+// Whether the few-row kernel takes a grouped call of `total` rows, rather than
+// the persistent one with its 128-row tiles.  The host does not know the routing.
+// With up to 2048 outputs a CU (two workgroups' chunks) it is the faster one
+// however the rows are spread, but for 12% at one size.  Above, where even routing
+// leaves an expert at most 4 rows, or 8, the line lies at twice and one and a
+// half times that: us here / there, E 128 N 2048 K 768, 512 rows 24.8 / 39.6 (on 8
+// experts 10.2 / 10.0); N 1536 K 2048, 512 rows 42.6 / 57.6 (16.1 / 14.1); E 64 N 1408
+// K 2048, 384 rows 25 / 34 (13.0 / 13.0).
+constexpr bool use_grouped_skinny(int64_t total, int E, int N, int cus) {
+  const int64_t outputs = total * (int64_t)N, limit = 2048 * (int64_t)cus;
+  if (((int64_t)E + total / 16) * (((int64_t)N + 31) / 32) > (1 << 23)) return false;   // the grid: 2^32 threads
+  return outputs <= limit || (total <= 4 * (int64_t)E && outputs <= 2 * limit) ||
+         (total <= 8 * (int64_t)E && 2 * outputs <= 3 * limit);
+}
+
+// ---------------------------------------------------------------------------
 // NVFP4 and HiF4 at prefill sizes, 256 rows x 64 NF columns (k_linear16)
 // ---------------------------------------------------------------------------
 

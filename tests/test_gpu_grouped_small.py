@@ -1,8 +1,7 @@
 """The grouped MXFP4 GEMM with few rows per expert against the fp64 oracle:
 experts with no rows, one, a full tile and several tiles (found by a scan, here
 over more than 64 experts too), row maps, ragged K (expert scales at any byte),
-both kernels (K split for few column groups, not for many) and each backbone
-form."""
+each configuration (columns, K splits) and each backbone form."""
 
 import numpy as np
 import pytest
@@ -23,6 +22,9 @@ pytestmark = pytest.mark.gpu
     (130, 384, 256, [0] * 70 + [300] + [0] * 57 + [212, 0]),   # 512 rows, the most
     (4, 64, 64, [0, 0, 0, 33]),                            # less than a panel
     (4, 64, 256, [0, 0, 0, 33]),
+    (6, 200, 1664, [20, 0, 3, 40, 1, 17]),                 # K in four parts, 13 panels
+    (6, 200, 1632, [20, 0, 3, 40, 1, 17]),
+    (3, 70, 1600, [1, 0, 2]),                              # 32 columns
 ])
 @pytest.mark.parametrize("gather", [True, False])
 @pytest.mark.parametrize("n,m,dense", [(2, 4, False), (4, 8, False), (4, 8, True)])

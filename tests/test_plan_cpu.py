@@ -34,6 +34,11 @@ void plan_skinny16(int64_t M, int N, int K, int form, int cus, int* out) {
   const Wide16 w = wide16(M, N, K, form, cus);
   out[0] = use_skinny16(M, N, K, form, cus), out[1] = w.mf, out[2] = w.nb, out[3] = w.ks;
 }
+// {few-row kernel or not, column fragments, K splits} of a grouped call
+void plan_grouped(int64_t total, int E, int N, int K, int cus, int* out) {
+  const GroupedCfg c = grouped_cfg(total, E, N, K, cus);
+  out[0] = use_grouped_skinny(total, E, N, cus), out[1] = c.nb, out[2] = c.ks;
+}
 // row and column tile of every id in [0, units)
 void walk(int units, int gx, int gy, int* mt, int* nt) {
   for (int id = 0; id < units; ++id) tile_in_groups(xcd_unit(id, units), gx, gy, mt[id], nt[id]);
@@ -52,7 +57,7 @@ def plan(tmp_path_factory):
     L = ctypes.CDLL(so)
     for f in (L.plan_mx8, L.plan_16):
         f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.c_int]
-    for f in (L.plan_skinny, L.plan_skinny16):
+    for f in (L.plan_skinny, L.plan_skinny16, L.plan_grouped):
         f.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     return L
 
@@ -178,3 +183,24 @@ def test_small_m_configurations_are_built(plan):
                     plan.plan_skinny16(M, N, K, form, 256, out)
                     assert tuple(out)[1:] in {(2, 1, 8), (2, 2, 8), (2, 4, 4), (4, 4, 4)}
                     assert form >= 2 or out[1] == 2
+
+
+@pytest.mark.parametrize("total,E,N,K,want", [
+    # a single expert with all rows has to be no slower than on the persistent kernel: 64 rows 42 / 21 us
+    (64, 8, 28672, 4096, None), (8, 8, 28672, 4096, (4, 4)),
+    (512, 32, 1536, 4096, None), (512, 16, 4096, 1024, None),
+    # many experts
+    (512, 128, 2048, 768, (4, 2)), (512, 128, 1536, 2048, (4, 4)), (1024, 256, 512, 1024, (4, 2)),
+    (768, 128, 2048, 768, None),
+    # few column groups
+    (64, 8, 2048, 4096, (2, 4)), (128, 8, 2048, 4096, (4, 4)), (8, 8, 4096, 14336, (2, 4)),
+    # what tests/test_gpu_grouped_small.py runs
+    (81, 6, 200, 1664, (4, 4)), (81, 6, 200, 1632, (4, 4)), (3, 3, 70, 1600, (2, 4)), (74, 8, 200, 256, (4, 2)),
+    (11, 4, 330, 1184, (2, 4)), (512, 130, 384, 256, (4, 2)),
+    # more threads than a launch may have
+    (8, 1024, 1 << 21, 32, None), (8, 8, 1 << 28, 32, None),
+])
+def test_grouped_choice(plan, total, E, N, K, want):
+    out = (ctypes.c_int * 3)()
+    plan.plan_grouped(total, E, N, K, 256, out)
+    assert (tuple(out)[1:] if out[0] else None) == want
