@@ -195,15 +195,17 @@ __global__ __launch_bounds__(256) void k_prep_silu_few(XSrc src, int M, int K, A
 
 __global__ void k_copy_f32(const float* src, float* dst) { *dst = *src; }
 
-constexpr int kAmaxWG = 1024;   // most workgroups, and partial maxima, of the pre-pass
+constexpr int kAmaxWG = 1024;   // most workgroups, and partial maxima, of the pre-pass (k_amax_rows: twice that)
 
 __global__ __launch_bounds__(256) void k_pts_finalize(const float* part, int n, float* ts) {
   __shared__ float wmax[4];
   float m = 0.0f;
+  for (int base = 0; base < n; base += kAmaxWG) {
 #pragma unroll
-  for (int i = 0; i < kAmaxWG / 256; ++i) {
-    const int j = (int)threadIdx.x + 256 * i;
-    if (j < n) m = fmaxf(m, part[j]);
+    for (int i = 0; i < kAmaxWG / 256; ++i) {
+      const int j = base + (int)threadIdx.x + 256 * i;
+      if (j < n) m = fmaxf(m, part[j]);
+    }
   }
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
@@ -316,6 +318,27 @@ __global__ __launch_bounds__(256) void k_amax_plain(XSrc src, int M, int K, floa
   __syncthreads();
   if (threadIdx.x == 0)
     out[blockIdx.y * gridDim.x + blockIdx.x] = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+}
+
+// The same with a row per wavefront and a block per lane, for many long rows:
+// there the SiLUs bound the pass, and it wants more wavefronts and no piece of
+// the loop per eight elements (SiLU.mul, K 14336: M 4096 75 us, 81 above; M 8192
+// 140, 160).
+template <int SRC>
+__global__ __launch_bounds__(256) void k_amax_rows(XSrc src, int M, int K, float* out) {
+  __shared__ float wmax[4];
+  const int lane = threadIdx.x & 63;
+  float m = 0.0f;
+  for (int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < M; row += (int64_t)gridDim.x * 4) {
+    for (int b = lane; b < K / 32; b += 64) {
+      uint4 q[4];
+      load_block<SRC>(src, row, b, q, false);
+      float y[32];
+      unpack_bf16x32(q, y);
+      m = fmaxf(m, absmax32(y));
+    }
+  }
+  amax_publish(m, out, wmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -662,7 +685,10 @@ static void go_amax(const XSrc& src, int M, int K, const uint16_t* gamma, float 
                     hipStream_t st) {
   float* part = reinterpret_cast<float*>(scratch);
   unsigned n;
-  if (gamma == nullptr) {
+  if (gamma == nullptr && K >= 8192 && M >= 4 * kAmaxWG) {
+    n = (unsigned)std::min<int64_t>(((int64_t)M + 3) / 4, 2 * kAmaxWG);
+    k_amax_rows<SRC><<<n, 256, 0, st>>>(src, M, K, part);
+  } else if (gamma == nullptr) {
     // x: a row's chunks of 2048 positions; y: rows, up to 1024 workgroups in all
     const unsigned gx = (unsigned)std::min((K + 2047) / 2048, 64);
     const unsigned gy = (unsigned)std::min<int64_t>(M, kAmaxWG / gx);

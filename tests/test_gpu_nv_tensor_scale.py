@@ -55,3 +55,21 @@ def test_tensor_scale(S, G, T, K, src):
     y = y[0] if isinstance(y, tuple) else y
     want = np.float32(np.abs(y).max()) / np.float32(2688.0)
     assert bits(G.host(a.tensor_scale)[0]) == bits(want)
+
+
+@pytest.mark.parametrize("T,K", [(4096, 8192), (8195, 8224)])
+@pytest.mark.parametrize("src", ["plain", "silu"])
+def test_tensor_scale_many_long_rows(S, T, K, src):
+    """A row per wavefront, and rows left over for a second round of them; h of SiLU.mul as the call writes it."""
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn((T, K), device="cuda", generator=g, dtype=torch.bfloat16)
+    x[-1, -1] = 300.0
+    if src == "plain":
+        y, a = x, S.sharq_prepare(x, None, 1e-6, 2, 4, "nv")
+    else:
+        y = torch.empty_like(x)
+        a = S.sharq_prepare_silu_mul(x, torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16), 2, 4, "nv",
+                                     h_out=y)
+    torch.cuda.synchronize()
+    want = np.float32(y.float().abs().amax().item()) / np.float32(2688.0)
+    assert bits(a.tensor_scale.cpu().numpy()[0]) == bits(want)
