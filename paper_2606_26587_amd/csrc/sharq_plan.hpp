@@ -19,6 +19,11 @@ constexpr int xcd_unit(int id, int units) {
   return x * q + (x < rem ? x : rem) + (id >> 3);
 }
 
+// A launch may have 2^32 threads at most.  The small-M kernels give few rows
+// many threads (up to 8 a column), so the widest layers stay with the tiled ones.
+constexpr int64_t kMaxThreads = (int64_t)1 << 31;
+constexpr bool small_m_columns(int N) { return 8 * (int64_t)N <= kMaxThreads; }
+
 // Tile u of a grid of gx by gy: groups of 4 row tiles, column by column, so
 // that 32 consecutive tiles (the workgroups of one XCD) are 4 by 8.
 constexpr void tile_in_groups(int u, int gx, int gy, int& mt, int& nt) {
@@ -48,7 +53,7 @@ constexpr Plan8 plan8(int64_t M, int N, int cus) {
   const int gy = (int)((M + kRows8 - 1) / kRows8);
   Plan8 best{};
   for (int nf = 4; nf >= 3; --nf) {
-    const int gx = (N + 64 * nf - 1) / (64 * nf);
+    const int gx = (int)(((int64_t)N + 64 * nf - 1) / (64 * nf));
     const int64_t tiles = (int64_t)gx * gy, r = tiles % cus;
     Plan8 p{nf, gx, gy, (int)tiles, (int)(tiles < cus ? tiles : cus), 0.0};
     p.us = (double)((tiles + cus - 1) / cus) * (nf == 4 ? 1.85 : 1.50);
@@ -108,6 +113,7 @@ constexpr SkinnyWide skinny_wide(int64_t M, int N, int K, int form, int cus) {
     // its ragged form needs the registers of two wavefronts: 22 us, 12 in the estimate, at 256 x 5000 x 2080
     if (K % 128 != 0 && c.mf == 2 && c.nb == 4 && c.ks == 4) continue;
     const int64_t wgs = ((int64_t)N + 16 * c.nb - 1) / (16 * c.nb) * ((M + 16 * c.mf - 1) / (16 * c.mf));
+    if (wgs * 64 * c.ks > kMaxThreads) continue;
     const double r = (double)((wgs + cus - 1) / cus);
     const double us = c.us[form][0] + c.us[form][1] * (r - 1.0) + c.us[form][2] * r * K / 4096.0;
     if (best.mf == 0 || us < best.us) best = {c.mf, c.nb, c.ks, us};
@@ -121,13 +127,14 @@ constexpr SkinnyWide skinny_wide(int64_t M, int N, int K, int form, int cus) {
 // within 3 to 6%).  form, main_form: what each of the two would read.
 constexpr bool use_skinny(int64_t M, int N, int K, int form, int main_form, int cus) {
   constexpr double kMain[3][3] = {{5.19, 0.553, 0.183}, {5.73, 0.686, 0.163}, {6.51, 0.709, 0.176}};
-  if (K < 128) return false;
+  if (K < 128 || !small_m_columns(N)) return false;
   if (M <= 32) return true;
   if (M > 4096) return false;
+  const SkinnyWide w = skinny_wide(M, N, K, form, cus);
   const int64_t tiles = ((M + 127) / 128) * (((int64_t)N + 255) / 256);
   const double rounds = (double)((tiles + cus - 1) / cus), fill = tiles < cus ? (double)tiles / (double)cus : 1.0;
   const double main_us = kMain[main_form][0] + K / 128.0 * rounds * (kMain[main_form][1] + kMain[main_form][2] * fill);
-  return 1.05 * skinny_wide(M, N, K, form, cus).us < main_us;
+  return w.mf != 0 && 1.05 * w.us < main_us;
 }
 
 // ---------------------------------------------------------------------------
@@ -158,7 +165,7 @@ constexpr GroupedCfg grouped_cfg(int64_t total, int E, int N, int K, int cus) {
 // K 2048, 384 rows 25 / 34 (13.0 / 13.0).
 constexpr bool use_grouped_skinny(int64_t total, int E, int N, int cus) {
   const int64_t outputs = total * (int64_t)N, limit = 2048 * (int64_t)cus;
-  if (((int64_t)E + total / 16) * (((int64_t)N + 31) / 32) > (1 << 23)) return false;   // the grid: 2^32 threads
+  if (((int64_t)E + total / 16) * (((int64_t)N + 31) / 32) * 256 > kMaxThreads) return false;
   return outputs <= limit || (total <= 4 * (int64_t)E && outputs <= 2 * limit) ||
          (total <= 8 * (int64_t)E && 2 * outputs <= 3 * limit);
 }
@@ -240,6 +247,7 @@ constexpr Wide16 wide16(int64_t M, int N, int K, int form, int cus) {
   for (const Cfg16& c : kCfg16) {
     const double(&t)[4] = c.us[K % 128 == 0 ? form : form + 3];   // the dense copy needs K a multiple of 128
     const int64_t wgs = ((int64_t)N + 16 * c.nb - 1) / (16 * c.nb) * ((M + 16 * c.mf - 1) / (16 * c.mf));
+    if (wgs * 64 * c.ks > kMaxThreads) continue;
     const double r = (double)((wgs + cus - 1) / cus), r2 = (double)((wgs + 2 * cus - 1) / (2 * cus));
     const double us = t[0] + t[1] * (r - 1.0) + (t[2] * r + t[3] * r2) * panels;
     if (best.mf == 0 || us < best.us) best = {c.mf, c.nb, c.ks, us};
@@ -253,8 +261,10 @@ constexpr Wide16 wide16(int64_t M, int N, int K, int form, int cus) {
 // 256 tiles (same shapes; nine in ten within 3 to 9%).
 constexpr bool use_skinny16(int64_t M, int N, int K, int form, int cus) {
   constexpr double kStart[4] = {6.0, 6.6, 7.2, 6.2}, kRagged[4] = {1.41, 1.23, 1.41, 1.90};
+  if (!small_m_columns(N)) return false;
   if (M <= 32) return true;
   if (M > 4096) return false;
+  const Wide16 w = wide16(M, N, K, form, cus);
   double main_us = 0.0;
   if (K % 128 == 0) {
     main_us = kStart[form] + plan16(M, N, form, cus).us * K / 32.0;
@@ -262,7 +272,7 @@ constexpr bool use_skinny16(int64_t M, int N, int K, int form, int cus) {
     const int64_t tiles = ((M + 127) / 128) * (((int64_t)N + 255) / 256);
     main_us = 9.6 + (double)((tiles + cus - 1) / cus) * kRagged[form] * K / 32.0;
   }
-  return wide16(M, N, K, form, cus).us < main_us;
+  return w.mf != 0 && w.us < main_us;
 }
 
 }  // namespace sharq

@@ -204,3 +204,20 @@ def test_grouped_choice(plan, total, E, N, K, want):
     out = (ctypes.c_int * 3)()
     plan.plan_grouped(total, E, N, K, 256, out)
     assert (tuple(out)[1:] if out[0] else None) == want
+
+
+@pytest.mark.parametrize("name,forms", [("plan_skinny", 3), ("plan_skinny16", 4)])
+def test_launches_stay_below_2_32_threads(plan, name, forms):
+    """Wide layers with few rows, which the tiled kernels take (N 2^30, K 32, one row: 18 GB of weight)."""
+    out = (ctypes.c_int * 4)()
+    for form in range(forms):
+        for M in (1, 16, 17, 32, 33, 100, 1000, 4096):
+            for logn in range(10, 31):
+                for N in (1 << logn, (1 << logn) - 1):
+                    for K in (128, 256, 4096):
+                        getattr(plan, name)(M, N, K, form, 256, out)
+                        small, mf, nb, ks = out
+                        if M > 32 and small:
+                            assert -(-N // (16 * nb)) * -(-M // (16 * mf)) * 64 * ks < 1 << 32
+                        if M <= 32:
+                            assert small == (8 * N < 1 << 32 and N <= 1 << 28)
