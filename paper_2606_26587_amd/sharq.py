@@ -103,16 +103,26 @@ def _check(status: int, where: str):
 # The calls below run once per layer and decode step, where a kernel takes 5 to
 # 10 us: they pass plain integers (ctypes converts them by argtypes) and ask
 # torch for the current stream's handle without building a Stream object (2.9
-# us of the 9.0 us a sharq_linear call took on the host; 6.4 us after).
+# us of the 9.0 us a sharq_linear call took on the host; 6.0 us after).
 
 def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+def _stream_handle(c=torch._C):
+    """The function that gives the current stream's handle: torch's raw accessors, which are not part of its
+    public interface, or the Stream object where a torch has none."""
+    raw, device = getattr(c, "_cuda_getCurrentRawStream", None), getattr(c, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+_current = _stream_handle()
+
+
 def _stream(stream):
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _current() if stream is None else stream.cuda_stream
 
 
 # ---------------------------------------------------------------------------
