@@ -349,7 +349,10 @@ SHARQ_API sharq_status sharq_prepare_silu_mul(const void *gate, const void *up, 
  * apply) multiplies the exactly dequantized values q * d on 16-bit matrix
  * cores (in fp16 or bf16, both exact for every q * d; where the kernel for large
  * M adds the two paths' values before it multiplies, only where that sum is
- * exact too) and applies S_x * S_w once to the fp32 sums.  NVFP4 needs
+ * exact too) and applies S_x * S_w once to the fp32 sums.  That choice is made
+ * for 32 consecutive rows together, from their block scales: at the same M a
+ * row's fp32 sums may be rounded in another order when other rows of its 32
+ * change, within the same error bound.  NVFP4 needs
  * a->tensor_scale and w->tensor_scale.  For the other modes of a->mode, Y is the sum over the
  * mode's paths, each against the weight's view of its kind (sparse view for a
  * sparse path, dense view for a dense one).

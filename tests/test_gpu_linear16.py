@@ -68,6 +68,40 @@ def test_linear16_half_tiles_compressed(S, G, n, m):
     check(S, G, o, O.quantize_weight(synth.weight(N, K, seed=7), "nv"), False, T, N, K, (torch.float32,))
 
 
+def crafted(T, K, sp, dn, seed=9, n=2, m=4):
+    """A prepared NVFP4 activation with the given scale codes ([T, K / 32] and [T, K / 16]) and random codes."""
+    rng = np.random.default_rng(seed)
+    keep = np.zeros((T, K // m, m), bool)
+    np.put_along_axis(keep, rng.random((T, K // m, m)).argsort(axis=2)[..., :n], True, axis=2)
+    keep = keep.reshape(T, K)
+    codes = np.where(keep, rng.integers(0, 16, size=(T, K)), 0).astype(np.uint8)
+    sp_codes, sp_meta = O.pack_backbone(codes, keep, n, m)
+    return {"rows": T, "K": K, "n": n, "m": m, "pairs": False, "fmt": "nv", "tensor_scale": np.float32(0.5),
+            "mode": "sharq", "sp_codes": sp_codes, "sp_meta": sp_meta, "sp_scale": sp.astype(np.uint8),
+            "dn_codes": O.pack_nibbles(rng.integers(0, 16, size=(T, K)).astype(np.uint8)),
+            "dn_scale": dn.astype(np.uint8), "dn_meta": np.zeros((T, 0), np.uint8)}
+
+
+def test_nv_row_beside_other_rows(S, G):
+    """Whether the paths are added is decided for 32 rows together: a row's sums may round otherwise beside
+    an outlier row, within the same bound; the rows of other groups keep their bits."""
+    T, N, K = 2100, 1992, 512
+    sp, dn = np.full((T, K // 32), 56), np.full((T, K // 16), 40)    # scales 1 and 1/4: added
+    a = crafted(T, K, sp, dn)
+    sp[37] = 112                                                     # 2^7 beside 1/4: apart
+    b = crafted(T, K, sp, dn)
+    wo = O.quantize_weight(synth.weight(N, K, seed=7), "nv")
+    w, ys = G.oracle_to_weight(wo), []
+    for o in (a, b):
+        ys.append(S.sharq_linear(G.oracle_to_act(o), w, dtype=torch.float32))
+        torch.cuda.synchronize()
+        rows = np.arange(96)
+        err = np.abs(G.host(ys[-1][:96]).astype(np.float64) - O.linear(o, wo, rows=rows))
+        # fp32 sums of 2K exact products and the tensor scales' two roundings
+        assert (err <= (2 * K + 2) * 2.0 ** -24 * O.linear_abs(o, wo, rows=rows)).all()
+    assert torch.equal(ys[0][:32], ys[1][:32]) and torch.equal(ys[0][64:], ys[1][64:])
+
+
 def test_nv_scales_around_the_merge_rule(S, G):
     """Block scales whose ratio runs from equal to far apart, constant over
     32 rows (the kernel decides for 32 rows together) or mixed, zero scales
