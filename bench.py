@@ -133,7 +133,8 @@ def weight_bytes(N, K, fmt="mx"):
 
 def gemm_source_digest():
     h = hashlib.sha256()
-    for name in ("sharq_gemm.hip", "sharq_linear16.hip", "sharq_mx8.hip", "sharq_tile.hpp"):
+    for name in ("sharq_gemm.hip", "sharq_linear16.hip", "sharq_mx8.hip", "sharq_tile.hpp", "sharq_plan.hpp",
+                 "sharq_dequant16.hpp", "sharq_device.hpp"):
         with open(os.path.join(ROOT, "paper_2606_26587_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -28,9 +28,7 @@
 // block.  Accumulator element r of lane l is output row
 // 8 (r / 4) + 4 (l / 32) + (r % 4), column l % 32.
 
-#include "sharq_plan.hpp"
 #include "sharq_tile.hpp"
-#include <type_traits>
 
 namespace sharq {
 
@@ -1206,19 +1204,13 @@ __global__ __launch_bounds__(256) void k_linear_mx_grouped_persist(
     const int64_t r_end = offs[e + 1];
     row_hi = row_lo + kBM < r_end ? row_lo + kBM : r_end;
   };
-  // XCD-contiguous numbering of the whole-tile units for any count: ids
-  // [0, 8 per) map one to one onto units, XCD x (id mod 8) taking units
-  // [x per, (x + 1) per); ids whose unit is past the last are skipped.
-  const int per = (full + 7) >> 3;
+  // each XCD takes a contiguous range of the whole-tile units (xcd_unit)
   int id = (int)blockIdx.x;
   tiles_mx_il<PAT, OutT, TAIL, GATHER ? 1 : 0>(sp_codes, sp_meta, sp_scale, dn_codes, dn_scale, act_rows, N, K, Y, ldy, lds,
                          lds + 3 * kStageBytes, lut48, [&](IlTile& t) {
-                           int u = full;
-                           while (u >= full) {
-                             if (id >= 8 * per) return false;
-                             u = (id & 7) * per + (id >> 3);
-                             id += G;
-                           }
+                           if (id >= full) return false;
+                           const int u = xcd_unit(id, full);
+                           id += G;
                            int e;
                            locate(u, e, t.row_lo, t.row_hi);
                            t.r = il_row(row_index, t.row_lo, t.row_hi);

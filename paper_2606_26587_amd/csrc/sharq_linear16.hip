@@ -7,9 +7,7 @@
 // in the epilogue.  K a multiple of 128 runs on the persistent kernel below in
 // fp16; other K on a double-buffered one in bf16.
 
-#include "sharq_plan.hpp"
 #include "sharq_tile.hpp"
-#include <type_traits>
 
 namespace sharq {
 
@@ -189,20 +187,6 @@ constexpr int kT16 = 512;                     // threads
 constexpr int kPart16 = 256 * 64;             // one operand of a step: 256 rows x 32 positions x 2 bytes
 constexpr int kStage16 = 3 * kPart16;         // activation (merged, or backbone), weight, residual
 constexpr int kLds16 = 3 * kStage16;          // 144 KB; the epilogue reuses it
-
-// Place of part q (16 bytes, 8 positions) of a staged 64-byte row: q ^
-// swz16(row).  Reads of 32 rows and writes of 16 rows then have no bank
-// conflict (with the places of the bf16 kernel above they took 17% of the
-// cycles).
-__device__ __forceinline__ int swz16(int row) { return ((row >> 2) ^ ((row >> 1) & 1)) & 3; }
-
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
 
 struct Args16 {
   const uint8_t *spc, *spm, *sps, *dnc, *dns, *wc, *ws;
@@ -454,16 +438,16 @@ __device__ __forceinline__ void tile16(const Args16& p, OutT* Y, int64_t ldy, in
   t.ws = p.ws + (int64_t)n0 * (4 * kSc);
 
   Put16 put;
-  put.a0 = (uint32_t)(arow * 64 + 16 * ((2 * (tid & 1)) ^ swz16(arow)));
-  put.a1 = (uint32_t)(arow * 64 + 16 * ((2 * (tid & 1) + 1) ^ swz16(arow)));
+  put.a0 = (uint32_t)(arow * 64 + 16 * ((2 * (tid & 1)) ^ swz_row(arow)));
+  put.a1 = (uint32_t)(arow * 64 + 16 * ((2 * (tid & 1) + 1) ^ swz_row(arow)));
   const int wq = NF == 2 ? tid % 4 : 2 * (tid & 1);
-  put.w0 = (uint32_t)(lrow * 64 + 16 * (wq ^ swz16(lrow)));
-  put.w1 = (uint32_t)(lrow * 64 + 16 * (((wq + 1) & 3) ^ swz16(lrow)));
+  put.w0 = (uint32_t)(lrow * 64 + 16 * (wq ^ swz_row(lrow)));
+  put.w1 = (uint32_t)(lrow * 64 + 16 * (((wq + 1) & 3) ^ swz_row(lrow)));
 
   // sub-step T: lane half h takes part 2 h + T of its row; fragments start at multiples of 32 rows
   const int col = lane & 31, half = lane >> 5;
-  const uint32_t rd0 = (uint32_t)(col * 64 + 16 * ((2 * half) ^ swz16(col)));
-  const uint32_t rd1 = (uint32_t)(col * 64 + 16 * ((2 * half + 1) ^ swz16(col)));
+  const uint32_t rd0 = (uint32_t)(col * 64 + 16 * ((2 * half) ^ swz_row(col)));
+  const uint32_t rd1 = (uint32_t)(col * 64 + 16 * ((2 * half + 1) ^ swz_row(col)));
   const uint32_t rd_a = (uint32_t)(wm * 64 * 64), rd_w = (uint32_t)(wn * 32 * NF * 64);
 
   v16f acc[2][NF];

@@ -16,9 +16,7 @@
 // 4096 52.4 -> 47.9 (NF 3: one round of 256 tiles); N 28672 219.9 -> 210.8; M 4096,
 // N 4096, K 4096 65.7 -> 59.7; M 2048, N 4096, K 14336 102.5, 111.3 here (NF 2).
 
-#include "sharq_plan.hpp"
 #include "sharq_tile.hpp"
-#include <type_traits>
 
 namespace sharq {
 
@@ -33,8 +31,6 @@ struct Args8 {
   int64_t M;
   int N, K;
 };
-
-__device__ __forceinline__ int swz8(int row) { return ((row >> 2) ^ ((row >> 1) & 1)) & 3; }
 
 // Direct loads from global memory to LDS: lane l's 16 (4) bytes at base + off
 // go to LDS address lds + 16 l (4 l).
@@ -102,14 +98,6 @@ __device__ __forceinline__ void read_scales8(Scales8<NF>& s, const uint8_t* stag
     s.w[f] = *reinterpret_cast<const uint32_t*>(p + 2 * kScale8 + (wrow + 32 * f) * 4) >> (16 * half);
 }
 
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for8(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for8<I + 1, N>(f);
-  }
-}
-
 template <int NF>
 struct Ops8 {
   uint4 sp[2], dn[2], b[NF];
@@ -126,7 +114,7 @@ __device__ __forceinline__ void read_op8(Ops8<NF>& o, const uint8_t* stage, uint
 template <int NF, int SUB>
 __device__ __forceinline__ void sub8(v16f (&acc)[2][NF], const Ops8<NF>& o, const Scales8<NF>& s, Ops8<NF>& n,
                                      const uint8_t* from, uint32_t rd, uint32_t rd_a, uint32_t rd_w) {
-  static_for8<0, 4 * NF>([&](auto ic) {
+  static_for<0, 4 * NF>([&](auto ic) {
     constexpr int i = decltype(ic)::value, j = i % (2 * NF), f = j >> 1, r = j & 1;
     if constexpr (i < 2 * NF) acc[r][f] = mma8<SUB>(o.b[f], o.sp[r], acc[r][f], s.w[f], s.sp[r]);
     else acc[r][f] = mma8<SUB>(o.b[f], o.dn[r], acc[r][f], s.w[f], s.dn[r]);
@@ -144,7 +132,7 @@ template <int NF>
 __device__ __forceinline__ void set_loader8(Loader8<NF>& ld, const Args8& p, const Tile8& t, int wave, int lane) {
   const int rows = (int)(p.M - t.row_lo < kRows8 ? p.M - t.row_lo : kRows8), cols = p.N - t.n0;
   const auto slice = [&](int row, int have) {   // rows past the last one reread it
-    return (uint32_t)((row < have ? row : have - 1) * 64 + 16 * ((lane & 3) ^ swz8(lane >> 2)));
+    return (uint32_t)((row < have ? row : have - 1) * 64 + 16 * ((lane & 3) ^ swz_row(lane >> 2)));
   };
   ld.wave = wave;
   ld.R = p.M;
@@ -172,8 +160,8 @@ __device__ __forceinline__ void tiles8(const Args8& p, OutT* Y, int64_t ldy, uin
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
   const int nks = p.K / 128;
-  const uint32_t rd0 = (uint32_t)(col * 64 + 16 * ((2 * half) ^ swz8(col)));
-  const uint32_t rd1 = (uint32_t)(col * 64 + 16 * ((2 * half + 1) ^ swz8(col)));
+  const uint32_t rd0 = (uint32_t)(col * 64 + 16 * ((2 * half) ^ swz_row(col)));
+  const uint32_t rd1 = (uint32_t)(col * 64 + 16 * ((2 * half + 1) ^ swz_row(col)));
   const uint32_t rd_a = (uint32_t)(wm * 64 * 64), rd_w = (uint32_t)(wn * 32 * NF * 64);
   const int arow = wm * 64 + col, wrow = wn * 32 * NF + col;
   const uint32_t l0 =
@@ -197,7 +185,7 @@ __device__ __forceinline__ void tiles8(const Args8& p, OutT* Y, int64_t ldy, uin
         for (int e = 0; e < 16; ++e) acc[r][f][e] = 0.0f;
     Ops8<NF> x, y;
     Scales8<NF> sc, sn;
-    static_for8<0, NF + 4>([&](auto j) { read_op8<NF, decltype(j)::value>(x, st0, rd0, rd_a, rd_w); });
+    static_for<0, NF + 4>([&](auto j) { read_op8<NF, decltype(j)::value>(x, st0, rd0, rd_a, rd_w); });
     read_scales8<NF>(sc, st0, arow, wrow, half);
     for (int s = 0; s < nks; ++s) {
       if (s + 2 < nks) ld.issue(q2, s + 2);

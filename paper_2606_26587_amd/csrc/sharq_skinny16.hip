@@ -21,7 +21,6 @@
 // Any K the formats allow: in a last panel narrower than 128, lanes whose
 // block lies past K reread block 0 and zero its weight codes.
 
-#include "sharq_plan.hpp"
 #include "sharq_tile.hpp"
 
 namespace sharq {

@@ -3,6 +3,9 @@
 #pragma once
 
 #include "sharq_dequant16.hpp"
+#include "sharq_plan.hpp"
+
+#include <type_traits>
 
 namespace sharq {
 
@@ -20,6 +23,20 @@ struct ARow {
 };
 
 #define SHARQ_FENCE() __builtin_amdgcn_sched_barrier(0)
+
+// f(std::integral_constant<int, I>{}) for I, ..., N - 1, unrolled.
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+// Place of part q (16 bytes) of a staged 64-byte row in the 8-wavefront kernels:
+// q ^ swz_row(row).  Reads of 32 rows and writes of 16 rows then have no bank
+// conflict (with the places of the bf16 kernels they took 17% of the cycles).
+__device__ __forceinline__ int swz_row(int row) { return ((row >> 2) ^ ((row >> 1) & 1)) & 3; }
 
 template <typename OutT>
 __device__ __forceinline__ void store_out(OutT* p, float v);
@@ -195,23 +212,6 @@ __device__ __forceinline__ void tile_of(int id, int gx, int gy, int& mt, int& nt
     mt = id / gx;
     nt = id - mt * gx;
   }
-}
-
-// The same order for any grid, for persistent loops: ids [0, 8 ceil(gx gy /
-// 8)) map one to one onto tile numbers, XCD x (id mod 8) taking a contiguous
-// range, walked in groups of 4 M-tiles, column by column (32 consecutive
-// numbers are 4 M-tiles x 8 N-tiles, as in tile_of, which this equals when
-// gx is a multiple of 8 and gy of 4).  False for the ids past the last tile.
-__device__ __forceinline__ bool tile_at(int id, int gx, int gy, int& mt, int& nt) {
-  const int total = gx * gy, per = (total + 7) >> 3;
-  const int u = (id & 7) * per + (id >> 3);
-  if (u >= total) return false;
-  const int g = u / (4 * gx), first = 4 * g;
-  const int gs = gy - first < 4 ? gy - first : 4;
-  const int in = u - g * 4 * gx;
-  mt = first + in % gs;
-  nt = in / gs;
-  return true;
 }
 
 // Half tile u of a last round run as `halves` half tiles behind `full` whole
