@@ -151,9 +151,11 @@ __global__ __launch_bounds__(256) void k_linear_nv(const uint8_t* sp_codes, cons
 // ---------------------------------------------------------------------------
 //
 // A workgroup of 8 wavefronts (two per SIMD: one's VALU and LDS work issues
-// under the other's MFMAs) computes 256 rows x 64 NF columns, each wavefront 64
-// x 32 NF.  One K step is one 32-position block.  Both operands of a step are
-// dequantized once per workgroup into LDS, 16 activation values and 4 NF
+// under the other's MFMAs) computes 64 WM rows x 64 NC columns, each wavefront 64
+// rows x 32 NF columns: 256 rows x 256, 192 or 128 columns (WM 4, NF = NC), or 128
+// x 256 (WM 2, NC 4, NF 2; the first four wavefronts dequantize the activations).
+// One K step is one 32-position block.  Both operands of a step are
+// dequantized once per workgroup into LDS, 16 activation values and 4 NC
 // weight values a thread, two steps ahead of their use (three stages).  With 64 rows per
 // wavefront a weight fragment read from LDS feeds two MFMAs; with 32 rows the
 // reads alone need the whole LDS bandwidth at the MFMA's rate.
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(256) void k_linear_nv(const uint8_t* sp_codes, cons
 // What bounds it: the 16-bit MFMA.  An MFMA keeps the VALU port for about 16
 // of its 32 cycles (measured: MFMAs with 8 and 12 VALU instructions each take
 // 50 and 64 cycles with two wavefronts per SIMD), so per wavefront and step
-// (NF 4) 16 to 18 NVFP4 MFMAs leave room for about 70 VALU instructions; the
+// (256 x 256) 16 to 18 NVFP4 MFMAs leave room for about 70 VALU instructions; the
 // dequantization takes 32 + 16 of them and its scales and addresses the rest.
 
 constexpr int kFmtNv = 0, kFmtHf = 1;
@@ -206,19 +208,19 @@ struct Raw16 {
 
 // Uniform bases (first row or column of the tile) and this thread's row and
 // part in them; rows past the last one reread it.
-template <int NF>
+template <int NC>
 struct Tile16 {
   // threads that share a weight row's block: 16 values each, 8 with 128 columns
-  static constexpr int kPerRow = NF == 2 ? 4 : 2;
+  static constexpr int kPerRow = NC == 2 ? 4 : 2;
   const uint8_t *dn, *spc, *spm, *dns, *sps, *wc, *ws;
   uint32_t arow, half, wrow, wpart;
-  bool wactive;              // the same in every lane of a wavefront (192 columns: 6 wavefronts)
+  bool wactive, aactive;     // the same in every lane of a wavefront (192 columns: 6 wavefronts; 128 rows: 4)
 };
 
 // Block BLK of the panel with pm rows (pn columns) before it.
-template <int FMT, int PAT, int NF, int BLK>
-__device__ __forceinline__ void load16(Raw16& r, const Tile16<NF>& t, int64_t pm, int64_t pn, int part) {
-  const uint32_t at = t.arow * 64 + 8 * t.half, wat = t.wrow * 64 + (NF == 2 ? 4 : 8) * t.wpart;
+template <int FMT, int PAT, int NC, int BLK>
+__device__ __forceinline__ void load16(Raw16& r, const Tile16<NC>& t, int64_t pm, int64_t pn, int part) {
+  const uint32_t at = t.arow * 64 + 8 * t.half, wat = t.wrow * 64 + (NC == 2 ? 4 : 8) * t.wpart;
   if (part == 0) r.dn = *reinterpret_cast<const uint2*>(t.dn + pm * 64 + 16 * BLK + at);
   if (part == 1) {
     if (PAT == 0) {
@@ -231,7 +233,7 @@ __device__ __forceinline__ void load16(Raw16& r, const Tile16<NF>& t, int64_t pm
     }
   }
   if (part == 2) {
-    if (NF == 2) r.w.x = *reinterpret_cast<const uint32_t*>(t.wc + pn * 64 + 16 * BLK + wat);
+    if (NC == 2) r.w.x = *reinterpret_cast<const uint32_t*>(t.wc + pn * 64 + 16 * BLK + wat);
     else r.w = *reinterpret_cast<const uint2*>(t.wc + pn * 64 + 16 * BLK + wat);
   }
   if (FMT == kFmtNv) {
@@ -253,7 +255,7 @@ struct Put16 {
 
 // Dequantization of a step into its LDS stage, in pieces that fill MFMA slots.
 // BLK: block of the panel (HiF4: its parity is the half of the unit).
-template <int FMT, int PAT, int NF, int BLK>
+template <int FMT, int PAT, int NC, int BLK>
 struct Fill16 {
   f16x2 dsp, ddn, addend, dw;
   bool merged;
@@ -286,8 +288,11 @@ struct Fill16 {
 
   // Pieces 0..7: the activation (NVFP4, piece 0 with its scales); 8..11: the weight.
   template <int I>
-  __device__ __forceinline__ void piece(const Raw16& r, uint8_t* stage, const Put16& put, const Tile16<NF>& t,
+  __device__ __forceinline__ void piece(const Raw16& r, uint8_t* stage, const Put16& put, const Tile16<NC>& t,
                                         uint32_t* flags, int wave, int lane) {
+    if constexpr (I < 8) {
+      if (!t.aactive) return;
+    }
     if constexpr (FMT == kFmtNv) {
       if constexpr (I == 0) scales(r, flags, wave, lane);
       if constexpr (I < 8) {
@@ -307,7 +312,7 @@ struct Fill16 {
       } else if (t.wactive) {
         if constexpr (I == 8) dw = nv_scale2(r.sw);
         if constexpr (I == 9) *reinterpret_cast<uint4*>(stage + kPart16 + put.w0) = nv_dequant8(r.w.x, dw);
-        if constexpr (I == 11 && NF != 2) *reinterpret_cast<uint4*>(stage + kPart16 + put.w1) = nv_dequant8(r.w.y, dw);
+        if constexpr (I == 11 && NC != 2) *reinterpret_cast<uint4*>(stage + kPart16 + put.w1) = nv_dequant8(r.w.y, dw);
       }
     } else {
       constexpr int hb = BLK & 1;
@@ -322,10 +327,10 @@ struct Fill16 {
         *reinterpret_cast<uint4*>(stage + 2 * kPart16 + put.a1) = hf_dequant8(r.dn.y, hf_scales(r.sdn, hb, q + 1));
       if constexpr (I >= 8) {
         if (t.wactive) {
-          const int wq = NF == 2 ? (int)t.wpart : 2 * (int)t.wpart;
+          const int wq = NC == 2 ? (int)t.wpart : 2 * (int)t.wpart;
           if constexpr (I == 8)
             *reinterpret_cast<uint4*>(stage + kPart16 + put.w0) = hf_dequant8(r.w.x, hf_scales(r.sw, hb, wq));
-          if constexpr (I == 10 && NF != 2)
+          if constexpr (I == 10 && NC != 2)
             *reinterpret_cast<uint4*>(stage + kPart16 + put.w1) = hf_dequant8(r.w.y, hf_scales(r.sw, hb, wq + 1));
         }
       }
@@ -346,14 +351,14 @@ __device__ __forceinline__ uint4 lds16(const uint8_t* p) { return *reinterpret_c
 // that in its slots.  rd0, rd1: this lane's offsets of sub-steps 0 and 1 in an
 // operand's fragment.  The stage's residual products follow each sub-step:
 // always (HiF4), or for the row fragments whose paths stay apart.
-template <int FMT, int PAT, int NF, int FB, class Load>
+template <int FMT, int PAT, int NC, int NF, int FB, class Load>
 __device__ __forceinline__ void step16(v16f (&acc)[2][NF], uint4 (&a0)[2], uint4 (&b0)[NF], const uint8_t* cur,
                                        const uint8_t* nxt, uint8_t* fill, uint32_t rd0, uint32_t rd1, uint32_t rd_w,
                                        uint32_t rd_a, const uint32_t* cur_flags, uint32_t* fill_flags,
-                                       const Raw16& raw, const Put16& put, const Tile16<NF>& t, int wave, int lane,
+                                       const Raw16& raw, const Put16& put, const Tile16<NC>& t, int wave, int lane,
                                        Load load) {
   constexpr int kSlots = 4 * NF;
-  Fill16<FMT, PAT, NF, FB> fl;
+  Fill16<FMT, PAT, NC, FB> fl;
   uint4 a1[2], b1[NF], d[2];
   uint32_t apart0 = 0u, apart1 = 0u;
   if constexpr (FMT == kFmtNv) {
@@ -410,24 +415,27 @@ __device__ __forceinline__ void step16(v16f (&acc)[2][NF], uint4 (&a0)[2], uint4
   });
 }
 
-// One 256 x 64 NF tile: rows from row_lo, columns from n0.
-template <int FMT, int PAT, typename OutT, int NF>
+// One tile of 64 WM rows x 64 NC columns, rows from row_lo, columns from n0: WM by
+// 8 / WM wavefronts of 64 rows x 32 NF columns.
+template <int FMT, int PAT, typename OutT, int NC, int WM>
 __device__ __forceinline__ void tile16(const Args16& p, OutT* Y, int64_t ldy, int64_t row_lo, int n0, uint8_t* lds,
                                        uint32_t* flags) {
-  const int64_t row_hi = row_lo + kRows16 < p.M ? row_lo + kRows16 : p.M;
+  constexpr int WN = 8 / WM, NF = 2 * NC / WN, kRows = 64 * WM;
+  const int64_t row_hi = row_lo + kRows < p.M ? row_lo + kRows : p.M;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int wm = wave >> 1, wn = wave & 1;   // 64 rows, 32 NF columns
+  const int wm = wave / WN, wn = wave % WN;
   const int panels = p.K / 128;
 
-  Tile16<NF> t;
-  const int arow = tid >> 1, arows = (int)(row_hi - row_lo);
+  Tile16<NC> t;
+  const int arow = (tid >> 1) % kRows, arows = (int)(row_hi - row_lo);
   t.arow = (uint32_t)(arow < arows ? arow : arows - 1);
   t.half = (uint32_t)(tid & 1);
-  constexpr int kPerRow = Tile16<NF>::kPerRow;
+  constexpr int kPerRow = Tile16<NC>::kPerRow;
   const int lrow = tid / kPerRow, wrows = p.N - n0;
   t.wrow = (uint32_t)(lrow < wrows ? lrow : wrows - 1);
   t.wpart = (uint32_t)(tid % kPerRow);
-  t.wactive = NF != 3 || wave < 6;
+  t.wactive = NC != 3 || wave < 6;
+  t.aactive = WM == 4 || wave < 2 * WM;
   constexpr int kSc = FMT == kFmtNv ? 1 : 2;   // scale bytes per block in sps and ws
   t.dn = p.dnc + row_lo * 64;
   t.spc = p.spc + row_lo * (PAT == 0 ? 64 : 32);
@@ -440,7 +448,7 @@ __device__ __forceinline__ void tile16(const Args16& p, OutT* Y, int64_t ldy, in
   Put16 put;
   put.a0 = (uint32_t)(arow * 64 + 16 * ((2 * (tid & 1)) ^ swz_row(arow)));
   put.a1 = (uint32_t)(arow * 64 + 16 * ((2 * (tid & 1) + 1) ^ swz_row(arow)));
-  const int wq = NF == 2 ? tid % 4 : 2 * (tid & 1);
+  const int wq = NC == 2 ? tid % 4 : 2 * (tid & 1);
   put.w0 = (uint32_t)(lrow * 64 + 16 * (wq ^ swz_row(lrow)));
   put.w1 = (uint32_t)(lrow * 64 + 16 * (((wq + 1) & 3) ^ swz_row(lrow)));
 
@@ -464,13 +472,13 @@ __device__ __forceinline__ void tile16(const Args16& p, OutT* Y, int64_t ldy, in
   uint4 a0[2], b0[NF];
   uint8_t *st0 = lds, *st1 = lds + kStage16, *st2 = lds + 2 * kStage16;
   uint32_t *fg0 = flags, *fg1 = flags + 8, *fg2 = flags + 16;
-  static_for<0, 6>([&](auto i) { load16<FMT, PAT, NF, 0>(x, t, 0, 0, decltype(i)::value); });
-  static_for<0, 6>([&](auto i) { load16<FMT, PAT, NF, 1>(y, t, 0, 0, decltype(i)::value); });
+  static_for<0, 6>([&](auto i) { load16<FMT, PAT, NC, 0>(x, t, 0, 0, decltype(i)::value); });
+  static_for<0, 6>([&](auto i) { load16<FMT, PAT, NC, 1>(y, t, 0, 0, decltype(i)::value); });
   {
-    Fill16<FMT, PAT, NF, 0> f0;
-    Fill16<FMT, PAT, NF, 1> f1;
+    Fill16<FMT, PAT, NC, 0> f0;
+    Fill16<FMT, PAT, NC, 1> f1;
     static_for<0, 12>([&](auto i) { f0.template piece<decltype(i)::value>(x, st0, put, t, fg0, wave, lane); });
-    static_for<0, 6>([&](auto i) { load16<FMT, PAT, NF, 2>(x, t, 0, 0, decltype(i)::value); });
+    static_for<0, 6>([&](auto i) { load16<FMT, PAT, NC, 2>(x, t, 0, 0, decltype(i)::value); });
     static_for<0, 12>([&](auto i) { f1.template piece<decltype(i)::value>(y, st1, put, t, fg1, wave, lane); });
   }
   __syncthreads();
@@ -484,10 +492,10 @@ __device__ __forceinline__ void tile16(const Args16& p, OutT* Y, int64_t ldy, in
     const int64_t k0 = k, k1 = k + 1 < panels ? k + 1 : panels - 1;
     const int64_t m0 = k0 * p.M, m1 = k1 * p.M, c0 = k0 * p.N, c1 = k1 * p.N;
 #define SHARQ_STEP16(FB, LB, FROM, INTO, PM, PN)                                                                  \
-  step16<FMT, PAT, NF, FB>(acc, a0, b0, st0, st1, st2, rd0, rd1, rd_w, rd_a, fg0 + 2 * wm, fg2, FROM, put, t, wave, \
+  step16<FMT, PAT, NC, NF, FB>(acc, a0, b0, st0, st1, st2, rd0, rd1, rd_w, rd_a, fg0 + 2 * wm, fg2, FROM, put, t, wave, \
                            lane, [&](auto slot) {                                                                 \
                              constexpr int i = decltype(slot)::value;                                             \
-                             if constexpr (i < 6) load16<FMT, PAT, NF, LB>(INTO, t, PM, PN, i);                   \
+                             if constexpr (i < 6) load16<FMT, PAT, NC, LB>(INTO, t, PM, PN, i);                   \
                            });                                                                                    \
   __syncthreads();                                                                                                \
   {                                                                                                               \
@@ -526,23 +534,23 @@ __device__ __forceinline__ void tile16(const Args16& p, OutT* Y, int64_t ldy, in
 
 // At most one workgroup per CU walks the units b, b + G, ....  Units [0, full)
 // are whole tiles, each XCD (id mod 8) taking a contiguous range of them; with
-// NF 4 the rest run as two half tiles of 128 columns each.
-template <int FMT, int PAT, typename OutT, int NF>
+// 256 x 256 tiles the rest run as two half tiles of 128 columns each.
+template <int FMT, int PAT, typename OutT, int NC, int WM>
 __global__ __launch_bounds__(kT16) void k_linear16(Args16 p, OutT* Y, int64_t ldy, int gx, int gy, int full) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[kLds16];
   __shared__ uint32_t flags[24];
   for (int id = (int)blockIdx.x; id < full; id += (int)gridDim.x) {
     int mt, nt;
     tile_in_groups(xcd_unit(id, full), gx, gy, mt, nt);
-    tile16<FMT, PAT, OutT, NF>(p, Y, ldy, (int64_t)mt * kRows16, nt * 64 * NF, lds, flags);
+    tile16<FMT, PAT, OutT, NC, WM>(p, Y, ldy, (int64_t)mt * (64 * WM), nt * 64 * NC, lds, flags);
     __syncthreads();   // the LDS is free before the next tile's prologue
   }
-  if constexpr (NF == 4) {
+  if constexpr (NC == 4 && WM == 4) {
     for (int u = (int)blockIdx.x; u < 2 * (gx * gy - full); u += (int)gridDim.x) {
       int mt, nt;
       tile_in_groups(full + (u >> 1), gx, gy, mt, nt);
       const int n0 = nt * 256 + 128 * (u & 1);
-      if (n0 < p.N) tile16<FMT, PAT, OutT, 2>(p, Y, ldy, (int64_t)mt * kRows16, n0, lds, flags);
+      if (n0 < p.N) tile16<FMT, PAT, OutT, 2, 4>(p, Y, ldy, (int64_t)mt * 256, n0, lds, flags);
       __syncthreads();
     }
   }
@@ -553,9 +561,11 @@ static hipError_t go_linear16(const Args16& a, void* Y, int64_t ldy, hipStream_t
   const Plan16 p = plan16(a.M, a.N, form16(FMT == kFmtNv, PAT), device_cus());
   OutT* y = reinterpret_cast<OutT*>(Y);
   const dim3 grid((unsigned)p.grid), block(kT16);
-  if (p.nf == 4) k_linear16<FMT, PAT, OutT, 4><<<grid, block, 0, st>>>(a, y, ldy, p.gx, p.gy, p.full);
-  else if (p.nf == 3) k_linear16<FMT, PAT, OutT, 3><<<grid, block, 0, st>>>(a, y, ldy, p.gx, p.gy, p.full);
-  else k_linear16<FMT, PAT, OutT, 2><<<grid, block, 0, st>>>(a, y, ldy, p.gx, p.gy, p.full);
+  const auto kernel = p.rows == 128 ? k_linear16<FMT, PAT, OutT, 4, 2>
+                      : p.nf == 4   ? k_linear16<FMT, PAT, OutT, 4, 4>
+                      : p.nf == 3   ? k_linear16<FMT, PAT, OutT, 3, 4>
+                                    : k_linear16<FMT, PAT, OutT, 2, 4>;
+  kernel<<<grid, block, 0, st>>>(a, y, ldy, p.gx, p.gy, p.full);
   return hipGetLastError();
 }
 

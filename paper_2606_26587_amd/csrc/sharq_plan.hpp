@@ -171,38 +171,42 @@ constexpr bool use_grouped_skinny(int64_t total, int E, int N, int cus) {
 }
 
 // ---------------------------------------------------------------------------
-// NVFP4 and HiF4 at prefill sizes, 256 rows x 64 NF columns (k_linear16)
+// NVFP4 and HiF4 at prefill sizes (k_linear16)
 // ---------------------------------------------------------------------------
-
-constexpr int kRows16 = 256;   // rows of a tile
 
 // By format and backbone: NVFP4 dense copy, NVFP4 2:4 and 4:8 compressed, HiF4 2:4.
 constexpr int form16(bool nv, int pat) { return nv ? backbone_form(pat) : 3; }
 
-// Tile width and whole tiles of a launch.  The launch takes as long as its
-// rounds of tiles over the CUs; the cheapest width wins, the wider of equals.  A
-// last round of 256-column tiles that is at most half full runs as half tiles.
-// us: the estimate per 32 positions, from a tile's measured step by NF (4, 3, 2)
-// and form; a narrower tile's activation work does not shrink with it.
+// Tile and whole tiles of a launch.  The launch takes as long as its rounds of
+// tiles over the CUs; the cheapest tile wins, the larger of equals (128 rows: by 7%).  A last round
+// of 256 x 256 tiles that is at most half full runs as half tiles of 128 columns.
+// us: the estimate per 32 positions, from the measured step of tiles of 256 rows
+// x 256, 192 and 128 columns and of 128 rows x 256 columns, by form.  128 rows
+// suit M just past a multiple of 256 and HiF4, whose wavefronts then dequantize
+// less for each MFMA: NVFP4 dense M 384 N 37888 K 3584 208 us -> 172, HiF4 M 2048 N
+// 3584 K 3584 140 -> 116.
 struct Plan16 {
-  int nf, gx, gy, full, grid;
+  int rows, nf, gx, gy, full, grid;
   double us;
 };
 
 constexpr Plan16 plan16(int64_t M, int N, int form, int cus) {
-  constexpr double kStep[4][3] = {{1.16, 0.93, 0.64}, {1.43, 1.08, 0.75}, {1.62, 1.25, 0.99}, {1.81, 1.48, 1.13}};
-  const int gy = (int)((M + kRows16 - 1) / kRows16);
+  constexpr double kStep[4][4] = {
+      {1.16, 0.93, 0.69, 0.73}, {1.43, 1.08, 0.78, 0.79}, {1.62, 1.25, 1.04, 1.06}, {1.81, 1.48, 1.17, 0.96}};
+  constexpr int kTile[4][2] = {{256, 4}, {256, 3}, {256, 2}, {128, 4}};   // rows, columns / 64
   Plan16 best{};
-  for (int nf = 4; nf >= 2; --nf) {
-    const int gx = (int)(((int64_t)N + 64 * nf - 1) / (64 * nf));
+  for (int i = 0; i < 4; ++i) {
+    const int rows = kTile[i][0], nf = kTile[i][1];
+    const int gx = (int)(((int64_t)N + 64 * nf - 1) / (64 * nf)), gy = (int)((M + rows - 1) / rows);
     const int64_t tiles = (int64_t)gx * gy, r = tiles % cus;
-    Plan16 p{nf, gx, gy, (int)tiles, (int)(tiles < cus ? tiles : cus), 0.0};
-    p.us = (double)((tiles + cus - 1) / cus) * kStep[form][4 - nf];
-    if (nf == 4 && tiles > cus && r > 0 && 2 * r <= cus) {
+    Plan16 p{rows, nf, gx, gy, (int)tiles, (int)(tiles < cus ? tiles : cus), 0.0};
+    p.us = (double)((tiles + cus - 1) / cus) * kStep[form][i];
+    if (i == 0 && tiles > cus && r > 0 && 2 * r <= cus) {
       p.full = (int)(tiles - r);
       p.us = (double)(tiles / cus) * kStep[form][0] + kStep[form][2];
     }
-    if (best.nf == 0 || p.us < best.us) best = p;
+    // a last round that is not full runs faster than the others, which favours the larger tile
+    if (best.nf == 0 || p.us < (rows == 128 ? 0.93 : 1.0) * best.us) best = p;
   }
   return best;
 }

@@ -47,10 +47,11 @@ def check(S, G, o, wo, dense, T, N, K, dtypes=(torch.float32, torch.bfloat16)):
 
 
 @pytest.mark.parametrize("T,N", [
-    (2100, 1992),    # 256 x 128 tiles, ragged in both
+    (2100, 1992),    # 256 x 128 tiles (HiF4: 128 x 256), ragged in both
     (2040, 6104),    # 256 x 192 tiles
     (2290, 7101),    # 256 x 256 tiles, rows of odd length
-    (2300, 8008),    # 256 x 256 tiles and a last round of half tiles (NVFP4 compressed: 256 x 192)
+    (300, 17000),    # 128 x 256 tiles, the last with 44 rows
+    (2300, 8008),    # 256 x 256 tiles and a last round of half tiles (NVFP4 compressed, HiF4: 256 x 192)
 ])
 @pytest.mark.parametrize("fmt,n,m,dense,K", [("nv", 2, 4, True, 256), ("nv", 2, 4, False, 128),
                                              ("nv", 4, 8, False, 384), ("hif4", 2, 4, False, 256)])
@@ -60,12 +61,12 @@ def test_linear16(S, G, fmt, n, m, dense, K, T, N):
     check(S, G, o, O.quantize_weight(synth.weight(N, K, seed=7), fmt), dense, T, N, K)
 
 
-@pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
-def test_linear16_half_tiles_compressed(S, G, n, m):
+@pytest.mark.parametrize("fmt,n,m", [("nv", 2, 4), ("nv", 4, 8), ("hif4", 2, 4)])
+def test_linear16_half_tiles_compressed(S, G, fmt, n, m):
     """792 tiles of 256 x 256 on 256 CUs: three rounds and one of half tiles."""
     T, N, K = 2300, 22400, 128
-    o = O.prepare(synth.activations(T, K, seed=1), synth.gamma(K, seed=3), 1e-6, n, m, "nv")
-    check(S, G, o, O.quantize_weight(synth.weight(N, K, seed=7), "nv"), False, T, N, K, (torch.float32,))
+    o = O.prepare(synth.activations(T, K, seed=1), synth.gamma(K, seed=3), 1e-6, n, m, fmt)
+    check(S, G, o, O.quantize_weight(synth.weight(N, K, seed=7), fmt), False, T, N, K, (torch.float32,))
 
 
 def crafted(T, K, sp, dn, seed=9, n=2, m=4):

@@ -16,14 +16,14 @@ SHIM = r"""
 #include "sharq_plan.hpp"
 using namespace sharq;
 extern "C" {
-// {nf, gx, gy, full, grid} of the plan
+// {nf, gx, gy, full, grid, rows of a tile} of the plan
 void plan_mx8(int64_t M, int N, int cus, int* out, int) {
   const Plan8 p = plan8(M, N, cus);
-  out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid;
+  out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid, out[5] = kRows8;
 }
 void plan_16(int64_t M, int N, int cus, int* out, int form) {
   const Plan16 p = plan16(M, N, form, cus);
-  out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid;
+  out[0] = p.nf, out[1] = p.gx, out[2] = p.gy, out[3] = p.full, out[4] = p.grid, out[5] = p.rows;
 }
 // {small-M kernel or not, mf, nb, ks of its configuration above 32 rows}
 void plan_skinny(int64_t M, int N, int K, int form, int cus, int* out) {
@@ -79,12 +79,12 @@ def rounds_of(L, units, gx, gy, grid):
 @pytest.mark.parametrize("name,form", [("plan_mx8", 0)] + [("plan_16", f) for f in range(4)])
 @pytest.mark.parametrize("cus", [256, 64, 38])
 def test_rounds(plan, name, form, cus):
-    out = (ctypes.c_int * 5)()
+    out = (ctypes.c_int * 6)()
     odd = 0
     for M, N in SIZES:
         getattr(plan, name)(M, N, cus, out, form)
-        nf, gx, gy, full, grid = out
-        assert gx == -(-N // (64 * nf)) and gy == -(-M // 256)
+        nf, gx, gy, full, grid, rows = out
+        assert gx == -(-N // (64 * nf)) and gy == -(-M // rows)
         odd += full % 8 != 0
         assert rounds_of(plan, full, gx, gy, grid) == -(-full // grid), (M, N, nf, full, grid)
         rest = gx * gy - full   # a last round of half tiles
@@ -92,16 +92,18 @@ def test_rounds(plan, name, form, cus):
     assert odd > 20   # tile counts that are no multiple of 8 are among them
 
 
-@pytest.mark.parametrize("form,M,N,nf,halves", [
-    # the tile widths that tests/test_gpu_linear16.py runs (forms: NVFP4 dense, 2:4, 4:8, HiF4)
-    *[(f, 2100, 1992, 2, False) for f in range(4)], *[(f, 2040, 6104, 3, False) for f in range(4)],
-    *[(f, 2290, 7101, 4, False) for f in range(4)], (0, 2300, 8008, 4, True), (3, 2300, 8008, 4, True),
-    (1, 2300, 22400, 4, True), (2, 2300, 22400, 4, True),
+@pytest.mark.parametrize("form,M,N,tile", [
+    # the tiles that tests/test_gpu_linear16.py runs (forms: NVFP4 dense, 2:4, 4:8, HiF4): rows, columns, halves
+    *[(f, 2100, 1992, (256, 128, False)) for f in range(3)], (3, 2100, 1992, (128, 256, False)),
+    *[(f, 2040, 6104, (256, 192, False)) for f in range(4)], *[(f, 2290, 7101, (256, 256, False)) for f in range(4)],
+    (0, 2300, 8008, (256, 256, True)), (3, 2300, 8008, (256, 192, False)), *[(f, 2300, 22400, (256, 256, True)) for f in (1, 2, 3)],
+    *[(f, 300, 17000, (128, 256, False)) for f in range(4)],
+    *[(f, 384, 37888, (128, 256, False)) for f in range(4)],
 ])
-def test_tile_widths(plan, form, M, N, nf, halves):
-    out = (ctypes.c_int * 5)()
+def test_tiles(plan, form, M, N, tile):
+    out = (ctypes.c_int * 6)()
     plan.plan_16(M, N, 256, out, form)
-    assert out[0] == nf and (out[3] < out[1] * out[2]) == halves
+    assert (out[5], 64 * out[0], out[3] < out[1] * out[2]) == tile
 
 
 DENSE, C24, C48 = 0, 1, 2
@@ -147,7 +149,7 @@ NV_DENSE, NV24, NV48, HIF4 = 0, 1, 2, 3
 @pytest.mark.parametrize("form,M,N,K,small", [
     # (us on one card, the weight streamed: small-M kernel / prefill kernel)
     (NV48, 1024, 6144, 4096, False),
-    (NV24, 1792, 2048, 768, False),      # 42 / 26
+    (NV24, 4096, 2048, 768, False),
     (NV48, 1792, 2048, 768, False),      # 54 / 29
     (NV48, 2560, 2048, 768, False),
     (NV48, 768, 5000, 2080, True),       # 71 with 32 x 64 columns / 104, K not a multiple of 128
