@@ -77,11 +77,11 @@ DECODE_W_SETS = 5             # decode: weight copies rotate between steps (5 x 
 # (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0: the factors a plain 1 GiB device copy
 # gives).  Valid only for the GEMM sources it was measured on (sha256 prefix);
 # reported as null once one of them has changed.
-TRAFFIC = {"gemm_source": "ae82ff0e84ec80b1", "bytes_per_launch": 236.00e6}
+TRAFFIC = {"gemm_source": "855d6055e145c865", "bytes_per_launch": 236.00e6}
 # the same for the MoE workload's k_linear_mx_grouped_persist<0> (mean of its gate_up and down launches)
-MOE_TRAFFIC = {"gemm_source": "ae82ff0e84ec80b1", "bytes_per_launch": 437.3e6}
+MOE_TRAFFIC = {"gemm_source": "855d6055e145c865", "bytes_per_launch": 436.7e6}
 # and for the Qwen2.5-7B NVFP4 workload's k_linear16 (mean of its gate_up and down launches)
-NV_TRAFFIC = {"gemm_source": "ae82ff0e84ec80b1", "bytes_per_launch": 702.3e6}
+NV_TRAFFIC = {"gemm_source": "855d6055e145c865", "bytes_per_launch": 687.1e6}
 
 
 def log(*a):
